@@ -332,15 +332,14 @@ inline void face_flux(const StageCtx& X, const HostPart& H, const double* c0, co
   double qL[NV], qR[NV];
   for (int v = 0; v < NV; ++v) {
     double ep, em, ep2, em2;
-    fvk::extrap<-1, double>(X.rc, c1[v] - c0[v], c2[v] - c1[v], ep, em);
-    fvk::extrap<-1, double>(X.rc, c2[v] - c1[v], c3[v] - c2[v], ep2, em2);
+    fvk::extrap(X.rc, c1[v] - c0[v], c2[v] - c1[v], ep, em);
+    fvk::extrap(X.rc, c2[v] - c1[v], c3[v] - c2[v], ep2, em2);
     qL[v] = c1[v] + ep;
     qR[v] = c2[v] - em2;
   }
   if (H.curv) {
-    double A, h;
-    fvk::M<double>::sqrt2(fvk::fmad(Sx, Sx, Sy * Sy), A, h);
-    const double iA = 2.0 * h;
+    double A, iA;
+    fvk::area_of<double>(fvk::fmad(Sx, Sx, Sy * Sy), A, iA);
     const double n[2] = {Sx * iA, Sy * iA};
     fvk::roe_flux<double, 2, -1>(qL, qR, n, A, X.K, F);
   } else if (axis == 0) {

@@ -205,9 +205,8 @@ template <typename T, int AX, bool CURV>
 __device__ __forceinline__ void face_flux(const FluxK<T>& K, const T (&qL)[4], const T (&qR)[4],
                                           double Sx, double Sy, double area, T (&G)[4]) {
   if constexpr (CURV) {
-    double A, h;
-    M<double>::sqrt2(fmad(Sx, Sx, Sy * Sy), A, h);
-    const double iA = 2.0 * h;
+    double A, iA;
+    area_of<T>(fmad(Sx, Sx, Sy * Sy), A, iA);
     const T n[2] = {T(Sx * iA), T(Sy * iA)};
     roe_flux<T, 2, -1>(qL, qR, n, T(A), K, G);
   } else {
@@ -365,11 +364,11 @@ __device__ __forceinline__ void tile2d(const DevTile& tl, const DevBlock* __rest
   fix_with(sd, B, twx, twy, qn);
 #pragma unroll
   for (int c = 0; c < 4; ++c) fix2<CURV>(se[c], B, ce[c]);
-  T epm1[4];  // + side extrapolation of cell j-1
+  T epm1[4];  // + side slope of cell j-1
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     T em;
-    extrap<LIM>(rc, T(qm1[v]) - T(qa[v]), T(q0[v]) - T(qm1[v]), epm1[v], em);
+    slopes<LIM>(rc, T(qm1[v]) - T(qa[v]), T(q0[v]) - T(qm1[v]), epm1[v], em);
   }
   // right neighbour's node of row j0 (the last lane takes the node right of the tile)
   double x0r = 0, y0r = 0;
@@ -448,9 +447,9 @@ __device__ __forceinline__ void tile2d(const DevTile& tl, const DevBlock* __rest
       for (int v = 0; v < 4; ++v) {
         const T a = T(qm1[v]), b = T(q0[v]), c = T(qn[v]);
         T em;
-        extrap<LIM>(rc, b - a, c - b, ep0[v], em);
-        qL[v] = a + epm1[v];
-        qR[v] = b - em;
+        slopes<LIM>(rc, b - a, c - b, ep0[v], em);
+        qL[v] = left_state<LIM>(rc, a, epm1[v]);
+        qR[v] = right_state<LIM>(rc, b, em);
       }
       face_flux<T, 1, CURV>(K, qL, qR, -(y0r - y0), x0r - x0, areaJ, Gj);
     }
@@ -460,10 +459,10 @@ __device__ __forceinline__ void tile2d(const DevTile& tl, const DevBlock* __rest
       for (int v = 0; v < 4; ++v) {
         const T c = T(q0[v]);
         T epl, eml, epc, emc;
-        extrap<LIM>(rc, qim1[v] - qim2[v], c - qim1[v], epl, eml);  // cell i-1
-        extrap<LIM>(rc, c - qim1[v], qip1[v] - c, epc, emc);        // cell i
-        qL[v] = qim1[v] + epl;
-        qR[v] = c - emc;
+        slopes<LIM>(rc, qim1[v] - qim2[v], c - qim1[v], epl, eml);  // cell i-1
+        slopes<LIM>(rc, c - qim1[v], qip1[v] - c, epc, emc);        // cell i
+        qL[v] = left_state<LIM>(rc, qim1[v], epl);
+        qR[v] = right_state<LIM>(rc, c, emc);
       }
       face_flux<T, 0, CURV>(K, qL, qR, y1 - y0, -(x1 - x0), areaI, Gi);
     }
@@ -475,10 +474,10 @@ __device__ __forceinline__ void tile2d(const DevTile& tl, const DevBlock* __rest
       for (int v = 0; v < 4; ++v) {
         const T a = T(ce[0][v]), b = T(ce[1][v]), c = T(ce[2][v]), d = T(ce[3][v]);
         T ep, em, ep2, em2;
-        extrap<LIM>(rc, b - a, c - b, ep, em);    // cell ir-1
-        extrap<LIM>(rc, c - b, d - c, ep2, em2);  // cell ir
-        qL[v] = b + ep;
-        qR[v] = c - em2;
+        slopes<LIM>(rc, b - a, c - b, ep, em);    // cell ir-1
+        slopes<LIM>(rc, c - b, d - c, ep2, em2);  // cell ir
+        qL[v] = left_state<LIM>(rc, b, ep);
+        qR[v] = right_state<LIM>(rc, c, em2);
       }
       face_flux<T, 0, CURV>(K, qL, qR, ey1 - ey0, -(ex1 - ex0), areaI, G);
 #pragma unroll

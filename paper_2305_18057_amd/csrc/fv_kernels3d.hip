@@ -175,10 +175,10 @@ __device__ __forceinline__ void sto3(double* base, unsigned off, double v) {
 template <int LIM, typename T>
 __device__ __forceinline__ void face_states(const Recon<T>& rc, T a, T b, T c, T d, T& qL, T& qR) {
   T ep, em, ep2, em2;
-  extrap<LIM>(rc, b - a, c - b, ep, em);    // cell of b
-  extrap<LIM>(rc, c - b, d - c, ep2, em2);  // cell of c
-  qL = b + ep;
-  qR = c - em2;
+  slopes<LIM>(rc, b - a, c - b, ep, em);    // cell of b
+  slopes<LIM>(rc, c - b, d - c, ep2, em2);  // cell of c
+  qL = left_state<LIM>(rc, b, ep);
+  qR = right_state<LIM>(rc, c, em2);
 }
 
 template <typename T>
@@ -333,7 +333,7 @@ __device__ void tile3d(const DevTile& tl, const DevBlock* __restrict__ blocks, D
   // ---- prologue: planes k0-2 .. k0+1 of the own column (the right-edge
   //      i-face of each plane comes from the helper wave)
   // the k-window: planes k-1, k, k+1 and the incoming k+2 live in the four
-  // buffers qb0..qb3, the + side extrapolations of planes k-1 and k in eb0,
+  // buffers qb0..qb3, the + side slopes of planes k-1 and k in eb0,
   // eb1; the buffers' roles rotate (below), the values stay in place
   double qa[5], qb0[5], qb1[5], qb2[5], qb3[5], un[5] = {0, 0, 0, 0, 0};
   const Src3 sa = src3_k(blocks, B, bin, ic, jc, k0 - 2);
@@ -350,7 +350,7 @@ __device__ void tile3d(const DevTile& tl, const DevBlock* __restrict__ blocks, D
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     T em;
-    extrap<LIM>(rc, T(qb0[v]) - T(qa[v]), T(qb1[v]) - T(qb0[v]), eb0[v], em);
+    slopes<LIM>(rc, T(qb0[v]) - T(qa[v]), T(qb1[v]) - T(qb0[v]), eb0[v], em);
     eb1[v] = T(0);
   }
   double rg[5] = {0, 0, 0, 0, 0};
@@ -366,7 +366,7 @@ __device__ void tile3d(const DevTile& tl, const DevBlock* __restrict__ blocks, D
   __syncthreads();
 
   // one plane; qm1, q0, qn: planes k-1, k, k+1, q2 receives plane k+2;
-  // epm1 / ep0: + side extrapolations of planes k-1 / k (ep0 is written).
+  // epm1 / ep0: + side slopes of planes k-1 / k (ep0 is written).
   // ROT: end by moving the window down one buffer (qm1 <- q0 <- qn <- q2,
   // epm1 <- ep0); without it the caller passes the next plane's roles.
   auto step = [&](auto first_t, auto last_t, auto rot_t, int r, double (&qm1)[5], double (&q0)[5],
@@ -401,9 +401,9 @@ __device__ void tile3d(const DevTile& tl, const DevBlock* __restrict__ blocks, D
         for (int v = 0; v < 5; ++v) {
           const T a = T(qm1[v]), b = T(q0[v]), c = T(qn[v]);
           T em;
-          extrap<LIM>(rc, b - a, c - b, ep0[v], em);
-          qL[v] = a + epm1[v];
-          qR[v] = b - em;
+          slopes<LIM>(rc, b - a, c - b, ep0[v], em);
+          qL[v] = left_state<LIM>(rc, a, epm1[v]);
+          qR[v] = right_state<LIM>(rc, b, em);
         }
         roe_flux<T, 3, 2>(qL, qR, nullptr, az, K, Gk);
       }

@@ -143,14 +143,13 @@ __device__ __forceinline__ void inv_flux3(const Recon<T>& rc, const FluxK<T>& K,
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     T ep, em, ep2, em2;
-    extrap<LIM, T>(rc, T(c1[v] - c0[v]), T(c2[v] - c1[v]), ep, em);
-    extrap<LIM, T>(rc, T(c2[v] - c1[v]), T(c3[v] - c2[v]), ep2, em2);
-    qL[v] = T(c1[v]) + ep;
-    qR[v] = T(c2[v]) - em2;
+    slopes<LIM, T>(rc, T(c1[v] - c0[v]), T(c2[v] - c1[v]), ep, em);
+    slopes<LIM, T>(rc, T(c2[v] - c1[v]), T(c3[v] - c2[v]), ep2, em2);
+    qL[v] = left_state<LIM>(rc, T(c1[v]), ep);
+    qR[v] = right_state<LIM>(rc, T(c2[v]), em2);
   }
-  double A, h;
-  M<double>::sqrt2(fmad(S[0], S[0], fmad(S[1], S[1], S[2] * S[2])), A, h);
-  const double iA = 2.0 * h;
+  double A, iA;
+  area_of<T>(fmad(S[0], S[0], fmad(S[1], S[1], S[2] * S[2])), A, iA);
   const T n[3] = {T(S[0] * iA), T(S[1] * iA), T(S[2] * iA)};
   roe_flux<T, 3, -1>(qL, qR, n, T(A), K, G);
 }

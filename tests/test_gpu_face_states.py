@@ -1,0 +1,36 @@
+"""Face states outside the physical range: the flux must turn them into NaN."""
+import numpy as np
+import pytest
+
+from paper_2305_18057_amd import cases as CS
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("precision", [CS.FP64, CS.FP32_FLUX])
+@pytest.mark.parametrize("axis", [0, 1])
+def test_negative_density_on_both_sides_is_nonphysical(precision, axis):
+    """Without a limiter the cells rho = 10, 1, 1, 10 give the middle face
+    rho_L = rho_R = 1.5 - 5 < 0 although every cell is physical.  The roots
+    of both densities are NaN there, so the residual is NaN on the two cells of
+    that face and the step is refused, as in the oracle."""
+    from oracle import oracle as O
+    from paper_2305_18057_amd import fv
+    n = 24
+    case = CS.vortex_2d(n, n, noise=0.0)
+    rho = np.full((n, n), 10.0)
+    line = [slice(None), slice(None)]
+    line[1 - axis] = slice(11, 13)
+    rho[tuple(line)] = 1.0
+    case.U0 = [CS.conserved(rho, [0.1, 0.2], 1.0)[:, None]]
+    prm = CS.Params(**{**case.params.__dict__, "limiter": CS.UNLIMITED, "precision": precision})
+    ref, _ = O.OracleGrid(case).residual(prm)
+    g = fv.Grid(case)
+    g.set_state(case.state_flat())
+    R, _ = g.residual(prm)
+    bad = ~np.isfinite(np.asarray(ref).reshape(4, n, n)[0])
+    assert bad.sum() == 2 * n
+    assert np.array_equal(~np.isfinite(R.reshape(4, n, n)[0]), bad)
+    with pytest.raises(fv.FVError) as e:
+        g.step(prm, 1)
+    assert e.value.status == fv.FV_E_NONPHYSICAL
