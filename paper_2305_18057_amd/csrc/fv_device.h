@@ -875,21 +875,20 @@ __host__ __device__ __forceinline__ double cell_dt_limit(const double* q, const 
 }
 
 // Viscous flux F_nu . S (Sec. 2) of a face from u, v, p/rho at its cells L,
-// R (centres dx, dy apart) and its nodes A, B (B - A turned by -90 degrees
-// is S): Green-Gauss gradients over the face's diamond, Stokes stresses
-// with constant mu, heat flux kq grad(p/rho).  Differences in FP64, the
-// rest in T.
+// R (centres dx, dy apart) and their difference wt between its nodes B and A
+// (B - A turned by -90 degrees is S): Green-Gauss gradients over the face's
+// diamond, Stokes stresses with constant mu, heat flux kq grad(p/rho).
+// Differences in FP64, the rest in T.
 template <typename T>
 __host__ __device__ __forceinline__ void visc_flux(const double* wL, const double* wR,
-                                                   const double* wA, const double* wB, double dx,
-                                                   double dy, double Sx, double Sy, T mu, T kq,
-                                                   T* F) {
+                                                   const double* wt, double dx, double dy, double Sx,
+                                                   double Sy, T mu, T kq, T* F) {
   const T tSx = T(Sx), tSy = T(Sy), tdx = T(dx), tdy = T(dy);
   const T iD = M<T>::rcp(fmad(tdx, tSx, tdy * tSy));
   T gx[3], gy[3];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const T a = T(wR[k] - wL[k]), t = T(wB[k] - wA[k]);
+    const T a = T(wR[k] - wL[k]), t = T(wt[k]);
     gx[k] = fmad(a, tSx, -(t * tdy)) * iD;
     gy[k] = fmad(a, tSy, t * tdx) * iD;
   }

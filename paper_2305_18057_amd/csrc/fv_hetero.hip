@@ -363,16 +363,17 @@ void host_stage(HostPart& H, Pool& pool, const StageCtx& X) {
   };
   auto visc_face = [&](int iL, int jL, int iR, int jR, int iA, int jA, int iB, int jB, double Sx,
                        double Sy, double* F) {
-    double wL[3], wR[3], wA[3], wB[3], Fv[4];
+    double wL[3], wR[3], wA[3], wB[3], wt[3], Fv[4];
+    node_w(iA, jA, wA);
+    node_w(iB, jB, wB);
     for (int k = 0; k < 3; ++k) {
       wL[k] = H.w(k, iL, jL);
       wR[k] = H.w(k, iR, jR);
+      wt[k] = wB[k] - wA[k];
     }
-    node_w(iA, jA, wA);
-    node_w(iB, jB, wB);
     const double dx = H.cx[H.ce(iR, jR)] - H.cx[H.ce(iL, jL)];
     const double dy = H.cy[H.ce(iR, jR)] - H.cy[H.ce(iL, jL)];
-    fvk::visc_flux<double>(wL, wR, wA, wB, dx, dy, Sx, Sy, X.mu, X.kq, Fv);
+    fvk::visc_flux<double>(wL, wR, wt, dx, dy, Sx, Sy, X.mu, X.kq, Fv);
     for (int v = 0; v < NV; ++v) F[v] -= Fv[v];
   };
   const bool reads_un = X.mode >= 2, low = X.mode >= 4, norms = X.mode <= 1,

@@ -6,11 +6,13 @@
 // has a source.
 //
 // One workgroup of 256 threads takes a tile (64 columns by n rows) in slabs
-// of 4 rows, one cell per thread:
+// of 4 rows, one cell per thread (lane = column, wave = row):
 //   1. the slab's state with a two-cell halo on every side (corner ghosts
-//      included) is resolved into LDS, then u, v, p/rho and the cell
-//      centres of the slab and its first halo ring, and the node
-//      coordinates of the slab;
+//      included), u, v and p/rho of the slab and one ring, and the nodes go
+//      to LDS.  Every load of a slab is issued before the first wait: rows are
+//      wave-uniform, so the source of a row (this block, a neighbour, a wall)
+//      is scalar work; the four halo columns of all rows are one wave's third
+//      cell per lane;
 //   2. every face of the slab gets its flux once: Roe's flux of the MUSCL
 //      face states (times |S|) minus the viscous flux F_nu . S, whose face
 //      gradients come from Green-Gauss over the face's diamond (the two
@@ -18,6 +20,17 @@
 //      cells around the node);
 //   3. each cell sums its four faces, updates its state (the stage kinds of
 //      the Euler kernel) and adds to the tile's partials.
+// Bound by VALU issue (1105 instructions per cell-stage, 45% of the issue
+// slots) and by the latency of a slab's loads.  With one load wait per slab
+// instead of six, no separate pass for the primitives and the cell centres
+// and the node differences formed directly, a stage of the 524,288-cell grid
+// takes 37 us (53 us, 1520 instructions before).  The viscous flux is nearer
+// to extended precision than with node values and centres (9e-15 against
+// 1.9e-14 of the momentum flux on that grid: fewer roundings of sums whose
+// differences matter).
+// Two barriers per slab.  What the update needs of the slab's LDS (volume,
+// own state) is read before the second one, so a wave may stage the next slab
+// while others still update.
 // Readings of the viscous flux: Stokes's hypothesis with constant mu;
 // Theta = tau u + (mu/Pr) gamma/(gamma-1) grad(p/rho); ghost-cell centres
 // across block links are the neighbour's, across periodic faces the image
@@ -40,29 +53,20 @@ constexpr int kQW = 64 + 4;         // state columns i0-2 .. i0+65
 constexpr int kQH = kNsRows + 4;    // state rows j0-2 .. j0+5
 constexpr int kWW = 64 + 2;         // primitive / centre columns i0-1 .. i0+64
 constexpr int kWH = kNsRows + 2;    // rows j0-1 .. j0+4
+constexpr int kNW = 64 + 3;         // node columns i0-1 .. i0+65
 
-// The face fluxes of a slab are formed in registers and then written over the
-// state and primitive arrays, which no thread reads any more by then (the
-// right and top edges have slots of their own): 51 KB per workgroup, three
-// workgroups per CU (their VGPR budget is the limit as well).
+// 53 KB per workgroup: three workgroups per CU, as many as their registers
+// allow.
 struct NsLds {
-  union {
-    struct {
-      double q[4][kQH][kQW];        // conserved state of the slab and its halo
-      double w[3][kWH][kWW];        // u, v, p/rho
-    } s;
-    struct {
-      double fi[4][kNsRows][65];    // i-face fluxes (flux times area, minus viscous)
-      double fj[4][kNsRows + 1][64];  // j-face fluxes
-    } f;
-  } u;
-  double cx[kWH][kWW], cy[kWH][kWW];  // cell centres
-  double nx[kNsRows + 3][67], ny[kNsRows + 3][67];  // nodes of the slab and one ring
+  double q[4][kQH][kQW];             // conserved state of the slab and its halo
+  double w[3][kWH][kWW];             // u, v, p/rho of the slab and one ring
+  double nx[kNsRows + 3][kNW], ny[kNsRows + 3][kNW];  // nodes of the slab and one ring
                                                     // (rows j0-1.., columns i0-1..)
-  double un[4][kNsRows][64];        // U^n of the slab (stage kinds that read it)
-  double er[4][kNsRows];            // fluxes of the slab's right edge
-  double et[4][64];                 // fluxes of the slab's top edge
-  double red[4][8];                 // per-wave partials
+  double fi[4][kNsRows][65];         // i-face fluxes (times area, minus viscous)
+  double fj[4][kNsRows][64];         // j-face fluxes at j-1/2 of each row
+  double gi[2][2][kNsRows];          // centres of the ghosts beyond i-min, i-max: [side][x, y]
+  double gj[2][2][64];               // and beyond j-min, j-max
+  double red[4][8];                  // per-wave partials
 };
 
 // node (i, j) of block B: stored coordinates, or the uniform lattice
@@ -237,6 +241,56 @@ __device__ void ns_centre(const DevBlock* __restrict__ blocks, const DevBlock& B
   }
 }
 
+// Where a line of cells beyond one face (or inside the block) is read from,
+// without touching memory: a row j of B (columns inside), or a column i (rows
+// inside).  kind 0 copy, 1 inflow state, 2 slip mirror, 3 no-slip mirror of
+// face f; p is the line's first cell, vs the variable stride, st the stride
+// along the line.
+struct NsLine {
+  const double* p;
+  long long vs;
+  int st, kind, f;
+};
+
+__device__ __forceinline__ NsLine ns_line(const DevBlock* __restrict__ blocks, const DevBlock& B, int buf,
+                                          int d, int x) {
+  const DevBlock* S = &B;
+  const int n0 = d == 0 ? B.ni : B.nj;
+  NsLine L;
+  L.kind = 0;
+  L.f = 0;
+  int along = x;
+  if (x < 0 || x >= n0) {
+    const int side = x < 0 ? 0 : 1, g = side == 0 ? -x : x - n0 + 1;
+    L.f = 2 * d + side;
+    const int bk = B.bc_kind[L.f];
+    if (bk == BC_BLOCK) S = &blocks[B.bc_nbr[L.f]];
+    const int n = d == 0 ? S->ni : S->nj;
+    if (bk == BC_PERIODIC || bk == BC_BLOCK) along = side == 0 ? n - g : g - 1;
+    else if (bk == BC_SLIPWALL || bk == BC_NOSLIP) along = side == 0 ? g - 1 : n - g;
+    else along = side == 0 ? 0 : n - 1;  // EXTRAP, or INFLOW (any valid line)
+    L.kind = bk == BC_INFLOW ? 1 : (bk == BC_SLIPWALL ? 2 : (bk == BC_NOSLIP ? 3 : 0));
+  }
+  L.p = S->u[buf] + (d == 0 ? (long long)along : (long long)along * S->ni);
+  L.vs = S->ncell;
+  L.st = d == 0 ? S->ni : 1;
+  return L;
+}
+
+// the rule of a line's cell at index t along it, applied to the copied state
+__device__ __forceinline__ void ns_fix(const NsLine& L, const DevBlock& B, int t, double* q) {
+  if (L.kind == 1) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) q[v] = B.bc_q[L.f][v];
+  } else if (L.kind == 2) {
+    double sx, sy;
+    wall_vec(B, L.f, t, sx, sy);
+    slip_mirror(q, sx, sy);
+  } else if (L.kind == 3) {
+    noslip_mirror<2>(q, B.bc_q[L.f]);
+  }
+}
+
 template <int LIM, typename T>
 __device__ __forceinline__ void inv_flux(const Recon<T>& rc, const FluxK<T>& K, const double* c0,
                                          const double* c1, const double* c2, const double* c3,
@@ -262,11 +316,10 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
   using SK = StageKind<MODE>;
   constexpr int bin = SK::bin;
   constexpr int bout = SK::bout;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const DevBlock& B = blocks[tl.blk];
+  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int lane = tid & 63;
+  int blk = tl.blk;
   if (MODE != 0 && I.stopped) return;
-  const int ni = B.ni;
-  const long long ncell = B.ncell;
   const int i0 = tl.i0, nc = tl.ncol;
   Recon<T> rc;
   rc.lim = I.limiter;
@@ -285,187 +338,242 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
   double dmin = INFINITY;
   int bad = 0;
 
+#pragma unroll 1
   for (int js = tl.j0; js < tl.j0 + tl.n; js += kNsRows) {
+    // what depends on the lane and the block's descriptor is formed per slab:
+    // hoisted out of this loop it would not fit the registers
+    asm volatile("" : "+v"(lane), "+s"(blk));
+    const DevBlock& B = blocks[blk];
+    const int ni = B.ni;
+    const long long ncell = B.ncell;
+    // the slab row of this wave: turned with the tile, so that the wave that
+    // also forms the top edge is not always on the same SIMD
+    const int wrow = (wv + tl.local) & (kNsRows - 1);
+    const bool act_i = lane < nc;
+    const int ic = act_i ? i0 + lane : ni - 1;  // own column (idle lanes: a valid one)
+    const int icn = min(i0 + lane, ni);         // own node column
+    const int nj = B.nj;
+    const bool curv = B.xn != nullptr;
+    // halo columns i0-2, i0-1, i0+nc, i0+nc+1: lane = 4 * row + which, in wave 1
+    const bool hwave = wv == 1;
+    const int hc = lane & 3, hrow = lane >> 2;
+    const int hcol = hc < 2 ? hc : nc + hc;     // its LDS column
+    const bool lo_edge = i0 == 0, hi_edge = i0 + nc == ni;
     const int nr = min(kNsRows, tl.j0 + tl.n - js);
-    // ---- 1. state of the slab and its halo, then u, v, p/rho, centres, nodes
-    for (int x = tid; x < (nr + 4) * (nc + 4); x += kNsThreads) {
-      const int r = x / (nc + 4), c = x - r * (nc + 4);
-      double q[4];
-      ns_cell(blocks, &B, bin, i0 - 2 + c, js - 2 + r, q);
+    // ---- 1. every load of the slab, then the ghost rules, then LDS
+    double qs[2][4], xs[2], ys[2], qh[4], xh = 0.0, yh = 0.0;
+    NsLine ln[2];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) L.u.s.q[v][r][c] = q[v];
-    }
-    // nodes of the slab and one ring around it (clamped into the block: the
-    // ring nodes outside it are never used); face vectors and volumes
-    for (int x = tid; x < (nr + 3) * (nc + 3); x += kNsThreads) {
-      const int r = x / (nc + 3), c = x - r * (nc + 3);
-      double xx, yy;
-      node_of(B, min(max(i0 - 1 + c, 0), ni), min(max(js - 1 + r, 0), B.nj), xx, yy);
-      L.nx[r][c] = xx;
-      L.ny[r][c] = yy;
-    }
-    if constexpr (SK::reads_un) {
-      for (int x = tid; x < nr * nc; x += kNsThreads) {
-        const int r = x / nc, c = x - r * nc;
-        const double* p = B.u[0] + (long long)(js + r) * ni + i0 + c;
+    for (int h = 0; h < 2; ++h) {  // rows js-2+wv and js+2+wv of the own column
+      const int r = wv + 4 * h;
+      ln[h].kind = 0;
+      if (r < nr + 4) {
+        ln[h] = ns_line(blocks, B, bin, 1, js - 2 + r);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) L.un[v][r][c] = ldg(p + v * ncell);
+        for (int v = 0; v < 4; ++v) qs[h][v] = ldg(ln[h].p + v * ln[h].vs + ic);
+      }
+      if (r < nr + 3) node_of(B, icn, min(max(js - 1 + r, 0), nj), xs[h], ys[h]);
+    }
+    NsLine lh;
+    lh.kind = 0;
+    const int hj = js - 2 + hrow;  // row of the halo cell
+    const bool hcell = hwave && hrow < nr + 4;
+    const bool hin = hj >= 0 && hj < nj;
+    if (hcell) {
+      // the four columns are the same for the whole wave: scalar sources
+      const NsLine l0 = ns_line(blocks, B, bin, 0, i0 - 2), l1 = ns_line(blocks, B, bin, 0, i0 - 1);
+      const NsLine l2 = ns_line(blocks, B, bin, 0, i0 + nc), l3 = ns_line(blocks, B, bin, 0, i0 + nc + 1);
+      lh.p = hc == 0 ? l0.p : (hc == 1 ? l1.p : (hc == 2 ? l2.p : l3.p));
+      lh.vs = hc == 0 ? l0.vs : (hc == 1 ? l1.vs : (hc == 2 ? l2.vs : l3.vs));
+      lh.st = hc == 0 ? l0.st : (hc == 1 ? l1.st : (hc == 2 ? l2.st : l3.st));
+      lh.kind = hc == 0 ? l0.kind : (hc == 1 ? l1.kind : (hc == 2 ? l2.kind : l3.kind));
+      lh.f = hc == 0 ? l0.f : (hc == 1 ? l1.f : (hc == 2 ? l2.f : l3.f));
+      const double* p = lh.p + (long long)min(max(hj, 0), nj - 1) * lh.st;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) qh[v] = ldg(p + v * lh.vs);
+      // node columns i0-1, i0+nc and i0+nc+1
+      if (hc > 0 && hrow < nr + 3)
+        node_of(B, hc == 1 ? max(i0 - 1, 0) : min(i0 + nc + hc - 2, ni), min(max(js - 1 + hrow, 0), nj),
+                xh, yh);
+    }
+    // centres of the ghosts beyond the block's faces (boundary tiles only)
+    if (mu > 0.0) {
+      if (wv == 2 && (lo_edge || hi_edge) && lane < 2 * kNsRows) {
+        const int side = lane >> 2, r = lane & 3;
+        if (r < nr && (side == 0 ? lo_edge : hi_edge)) {
+          double cx, cy;
+          ns_centre(blocks, B, side == 0 ? -1 : ni, js + r, cx, cy);
+          L.gi[side][0][r] = cx;
+          L.gi[side][1][r] = cy;
+        }
+      }
+      if (((wv == 0 && js == 0) || (wv == 3 && js + nr == nj)) && act_i) {
+        const int side = wv == 0 ? 0 : 1;
+        double cx, cy;
+        ns_centre(blocks, B, i0 + lane, side == 0 ? -1 : nj, cx, cy);
+        L.gj[side][0][lane] = cx;
+        L.gj[side][1][lane] = cy;
       }
     }
-    __syncthreads();
-    // u, v, p/rho and the centres of the slab's cells and their ring: a
-    // centre inside the block from the staged nodes (the four around it, in
-    // the order of centre_of), a ghost centre by its rule
-    for (int x = tid; x < (nr + 2) * (nc + 2); x += kNsThreads) {
-      const int r = x / (nc + 2), c = x - r * (nc + 2);
-      const int ci = i0 - 1 + c, cj = js - 1 + r;
-      double cx, cy;
-      if (ci >= 0 && ci < ni && cj >= 0 && cj < B.nj) {
-        cx = 0.25 * (((L.nx[r][c] + L.nx[r][c + 1]) + L.nx[r + 1][c]) + L.nx[r + 1][c + 1]);
-        cy = 0.25 * (((L.ny[r][c] + L.ny[r][c + 1]) + L.ny[r + 1][c]) + L.ny[r + 1][c + 1]);
-      } else {
-        ns_centre(blocks, B, ci, cj, cx, cy);
+    // u, v, p/rho of a staged cell
+    auto put_cell = [&](const double* q, int r, int c) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) L.q[v][r][c] = q[v];
+      if (r >= 1 && r <= nr + 2 && c >= 1 && c <= nc + 2) {
+        const double ir = M<double>::rcp(q[0]);
+        const double u = q[1] * ir, v = q[2] * ir;
+        const double p = (gamma - 1.0) * (q[3] - 0.5 * q[0] * (u * u + v * v));
+        L.w[0][r - 1][c - 1] = u;
+        L.w[1][r - 1][c - 1] = v;
+        L.w[2][r - 1][c - 1] = p * ir;
       }
-      L.cx[r][c] = cx;
-      L.cy[r][c] = cy;
-      const double rho = L.u.s.q[0][r + 1][c + 1];
-      const double ir = M<double>::rcp(rho);
-      const double u = L.u.s.q[1][r + 1][c + 1] * ir, v = L.u.s.q[2][r + 1][c + 1] * ir;
-      const double p = (gamma - 1.0) * (L.u.s.q[3][r + 1][c + 1] - 0.5 * rho * (u * u + v * v));
-      L.u.s.w[0][r][c] = u;
-      L.u.s.w[1][r][c] = v;
-      L.u.s.w[2][r][c] = p * ir;
+    };
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = wv + 4 * h;
+      if (r < nr + 4 && act_i) {
+        if (ln[h].kind != 0) ns_fix(ln[h], B, ic, qs[h]);
+        put_cell(qs[h], r, lane + 2);
+      }
+      if (r < nr + 3 && act_i) {
+        L.nx[r][lane + 1] = xs[h];
+        L.ny[r][lane + 1] = ys[h];
+      }
+    }
+    if (hcell) {
+      if (!hin) ns_cell(blocks, &B, bin, i0 - 2 + hcol, hj, qh);  // a corner: both rules
+      else if (lh.kind != 0) ns_fix(lh, B, hj, qh);
+      put_cell(qh, hrow, hcol);
+      if (hc > 0 && hrow < nr + 3) {
+        const int c = hc == 1 ? 0 : nc + hc - 1;
+        L.nx[hrow][c] = xh;
+        L.ny[hrow][c] = yh;
+      }
     }
     __syncthreads();
 
-    // ---- 2. face fluxes, one thread per cell (its left and bottom faces;
-    //         the right column and top row also take the far faces)
-    const int li = lane, lj = wv;
-    const bool act = li < nc && lj < nr;
-    // node value (u, v, p/rho) of node (c, r) in w coordinates: mean of the
-    // cells (c-1, r-1), (c, r-1), (c-1, r), (c, r)
-    auto node_w = [&](int c, int r, double* o) {
+    // ---- 2. face fluxes, one thread per cell: its left and bottom faces
+    const int li = lane, lj = wrow;
+    const bool act = act_i && lj < nr;
+    const long long ro = (long long)(js + lj) * ni + ic;
+    double un[4] = {0, 0, 0, 0};
+    if constexpr (SK::reads_un) {  // used after the fluxes
+      if (act) {
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
-        o[k] = 0.25 * (((L.u.s.w[k][r - 1][c - 1] + L.u.s.w[k][r - 1][c]) + L.u.s.w[k][r][c - 1]) + L.u.s.w[k][r][c]);
-    };
-    // i-face at node column fc (0..nc) of slab row `row`
-    auto iface = [&](int fc, int row, double (&F)[4]) {
-      const int qr = row + 2, wr = row + 1;
+        for (int v = 0; v < 4; ++v) un[v] = ldg(B.u[0] + v * ncell + ro);
+      }
+    }
+    // The faces of a wave, one face per lane and pass: its row's i-faces, for
+    // the slab's first row the right edge (one row per lane), its row's
+    // j-faces, and for the slab's last row the top edge.  Both directions run the
+    // same code with the strides of their normal (n) and of the way from
+    // node A to node B of the face (t): unrolled per direction, the passes
+    // overlap and their registers spill.
+    double Fo[4] = {0, 0, 0, 0}, qin[4];
+#pragma unroll 1
+    for (int pass = 0; pass < 4; ++pass) {
+      if (pass == 1 && lj != 0) continue;
+      if (pass == 3 && lj != nr - 1) break;
+      const bool di = pass < 2;                                 // i-faces
+      const int fr = pass == 1 ? lane : (pass == 3 ? nr : lj);  // face row
+      const int fc = pass == 1 ? nc : lane;                     // face column
+      if (pass == 1 ? lane >= nr : !act) continue;
+      const int sq = di ? 1 : kQW;
+      const double* q = di ? &L.q[0][fr + 2][fc] : &L.q[0][fr][fc + 2];
       double c0[4], c1[4], c2[4], c3[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        c0[v] = L.u.s.q[v][qr][fc];
-        c1[v] = L.u.s.q[v][qr][fc + 1];
-        c2[v] = L.u.s.q[v][qr][fc + 2];
-        c3[v] = L.u.s.q[v][qr][fc + 3];
+        c0[v] = q[v * kQH * kQW];
+        c1[v] = q[v * kQH * kQW + sq];
+        c2[v] = q[v * kQH * kQW + 2 * sq];
+        c3[v] = q[v * kQH * kQW + 3 * sq];
       }
-      // area vector: from the nodes, or exactly h_y e_x on a uniform block
-      const double Sx = B.xn ? L.ny[row + 2][fc + 1] - L.ny[row + 1][fc + 1] : B.area[0];
-      const double Sy = B.xn ? -(L.nx[row + 2][fc + 1] - L.nx[row + 1][fc + 1]) : 0.0;
+      // nodes A and B: the area vector is B - A turned by -90 degrees (on a
+      // uniform block exactly the axis times the spacing)
+      const int A = di ? (fr + 1) * kNW + fc + 1 : (fr + 1) * kNW + fc + 2;
+      const int t = di ? kNW : -1, n = di ? 1 : kNW;
+      const double* X = &L.nx[0][0] + A;
+      const double* Y = &L.ny[0][0] + A;
+      const double Sx = curv ? Y[t] - Y[0] : (di ? B.area[0] : 0.0);
+      const double Sy = curv ? -(X[t] - X[0]) : (di ? 0.0 : B.area[1]);
       T G[4];
       inv_flux<LIM, T>(rc, K, c0, c1, c2, c3, Sx, Sy, G);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) F[v] = (double)G[v];
+      for (int v = 0; v < 4; ++v) Fo[v] = (double)G[v];
       if (mu > 0.0) {
-        double wL[3], wR[3], wA[3], wB[3];
+        // difference between the nodes' values: the face's own two cells
+        // cancel, a quarter of the cells beside them is left
+        const int tw = di ? kWW : -1, nw = di ? 1 : kWW;
+        const double* w = di ? &L.w[0][fr + 1][fc] : &L.w[0][fr][fc + 1];
+        double wL[3], wR[3], wt[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          wL[k] = L.u.s.w[k][wr][fc];
-          wR[k] = L.u.s.w[k][wr][fc + 1];
+          const double* wk = w + k * kWH * kWW;
+          wL[k] = wk[0];
+          wR[k] = wk[nw];
+          wt[k] = 0.25 * ((wk[tw] + wk[nw + tw]) - (wk[-tw] + wk[nw - tw]));
         }
-        node_w(fc + 1, wr, wA);      // node (i, j)
-        node_w(fc + 1, wr + 1, wB);  // node (i, j+1)
-        const double dx = L.cx[wr][fc + 1] - L.cx[wr][fc], dy = L.cy[wr][fc + 1] - L.cy[wr][fc];
-        T Fv[4];
-        visc_flux<T>(wL, wR, wA, wB, dx, dy, Sx, Sy, tmu, kq, Fv);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) F[v] -= (double)Fv[v];
-      }
-    };
-    // j-face at node row fr (0..nr) of slab column li
-    auto jface = [&](int fr, double (&F)[4]) {
-      const int qc = li + 2, wc = li + 1;
-      double c0[4], c1[4], c2[4], c3[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        c0[v] = L.u.s.q[v][fr][qc];
-        c1[v] = L.u.s.q[v][fr + 1][qc];
-        c2[v] = L.u.s.q[v][fr + 2][qc];
-        c3[v] = L.u.s.q[v][fr + 3][qc];
-      }
-      const double Sx = B.xn ? -(L.ny[fr + 1][li + 2] - L.ny[fr + 1][li + 1]) : 0.0;
-      const double Sy = B.xn ? L.nx[fr + 1][li + 2] - L.nx[fr + 1][li + 1] : B.area[1];
-      T G[4];
-      inv_flux<LIM, T>(rc, K, c0, c1, c2, c3, Sx, Sy, G);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) F[v] = (double)G[v];
-      if (mu > 0.0) {
-        double wL[3], wR[3], wA[3], wB[3];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          wL[k] = L.u.s.w[k][fr][wc];
-          wR[k] = L.u.s.w[k][fr + 1][wc];
+        // between the centres: the face's own nodes cancel likewise
+        double dx = 0.25 * ((X[n] + X[t + n]) - (X[-n] + X[t - n]));
+        double dy = 0.25 * ((Y[n] + Y[t + n]) - (Y[-n] + Y[t - n]));
+        const bool lo = di ? lo_edge && fc == 0 : js + fr == 0;
+        if (lo || (di ? hi_edge && fc == nc : js + fr == nj)) {
+          // the ghost's centre and the inside cell's (half the sums of its
+          // two nodes on the face and two beyond)
+          const int m = lo ? n : -n;
+          const double cx = 0.25 * ((X[0] + X[t]) + (X[m] + X[t + m]));
+          const double cy = 0.25 * ((Y[0] + Y[t]) + (Y[m] + Y[t + m]));
+          const double* gc = di ? &L.gi[lo ? 0 : 1][0][fr] : &L.gj[lo ? 0 : 1][0][fc];
+          const double gx = gc[0], gy = gc[di ? kNsRows : 64];
+          dx = lo ? cx - gx : gx - cx;
+          dy = lo ? cy - gy : gy - cy;
         }
-        node_w(wc + 1, fr + 1, wA);  // node (i+1, j)
-        node_w(wc, fr + 1, wB);      // node (i, j)
-        const double dx = L.cx[fr + 1][wc] - L.cx[fr][wc], dy = L.cy[fr + 1][wc] - L.cy[fr][wc];
         T Fv[4];
-        visc_flux<T>(wL, wR, wA, wB, dx, dy, Sx, Sy, tmu, kq, Fv);
+        visc_flux<T>(wL, wR, wt, dx, dy, Sx, Sy, tmu, kq, Fv);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) F[v] -= (double)Fv[v];
+        for (int v = 0; v < 4; ++v) Fo[v] -= (double)Fv[v];
       }
-    };
-    double Fl[4], Fb[4], qin[4];
-    // the slab's right-edge i-faces, one row per lane, in wave 0, and its
-    // top-edge j-faces in the top row's wave: each edge costs one wave-wide
-    // flux, where a right-edge face in every wave's last lane cost four
-    if (wv == 0 && lane < nr) {
-      double Fr[4];
-      iface(nc, lane, Fr);
+      if (pass != 3) {  // (the top edge stays in the registers of its row)
+        double* F = di ? &L.fi[0][fr][fc] : &L.fj[0][fr][fc];
+        const int sv = di ? kNsRows * 65 : kNsRows * 64;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) L.er[v][lane] = Fr[v];
-    }
-    if (act) {
-      if (lj == nr - 1) {
-        double Ft[4];
-        jface(nr, Ft);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) L.et[v][li] = Ft[v];
+        for (int v = 0; v < 4; ++v) F[v * sv] = Fo[v];
       }
-      iface(li, lj, Fl);
-      jface(lj, Fb);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) qin[v] = L.u.s.q[v][lj + 2][li + 2];
     }
-    __syncthreads();  // state and primitives are read no more: the fluxes take their place
+    double vol = B.vol;
     if (act) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        L.u.f.fi[v][lj][li] = Fl[v];
-        L.u.f.fj[v][lj][li] = Fb[v];
-      }
+      for (int v = 0; v < 4; ++v) qin[v] = L.q[v][lj + 2][li + 2];
+    }
+    // nodes of the own cell (0.5 times the sums of opposite ones are its
+    // mean area vectors)
+    double xa = 0, ya = 0, xb = 0, yb = 0, xc = 0, yc = 0, xd = 0, yd = 0;
+    if (curv && act) {
+      xa = L.nx[lj + 1][li + 1], ya = L.ny[lj + 1][li + 1];
+      xb = L.nx[lj + 1][li + 2], yb = L.ny[lj + 1][li + 2];
+      xc = L.nx[lj + 2][li + 1], yc = L.ny[lj + 2][li + 1];
+      xd = L.nx[lj + 2][li + 2], yd = L.ny[lj + 2][li + 2];
+      vol = 0.5 * fmad(xd - xa, yc - yb, -((xc - xb) * (yd - ya)));
+    }
+    double Sb[2][3];
+    if constexpr (SK::cfl) {
+      Sb[0][0] = curv ? 0.5 * ((yc - ya) + (yd - yb)) : B.area[0];
+      Sb[0][1] = curv ? -0.5 * ((xc - xa) + (xd - xb)) : 0.0;
+      Sb[1][0] = curv ? -0.5 * ((yb - ya) + (yd - yc)) : 0.0;
+      Sb[1][1] = curv ? 0.5 * ((xb - xa) + (xd - xc)) : B.area[1];
+      Sb[0][2] = Sb[1][2] = 0.0;
     }
     __syncthreads();
 
     // ---- 3. residual, update, partials
     if (act) {
-      const int i = i0 + li, j = js + lj;
       double R[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
-      {
-        const double fr = li == nc - 1 ? L.er[v][lj] : L.u.f.fi[v][lj][li + 1];
-        const double ft = lj == nr - 1 ? L.et[v][li] : L.u.f.fj[v][lj + 1][li];
-        R[v] = (0.0 + (fr - Fl[v])) + (ft - Fb[v]);
+      for (int v = 0; v < 4; ++v) {
+        const double ft = lj == nr - 1 ? Fo[v] : L.fj[v][lj + 1][li];
+        R[v] = (0.0 + (L.fi[v][lj][li + 1] - L.fi[v][lj][li])) + (ft - L.fj[v][lj][li]);
       }
-      const double xa = L.nx[lj + 1][li + 1], ya = L.ny[lj + 1][li + 1];
-      const double xb = L.nx[lj + 1][li + 2], yb = L.ny[lj + 1][li + 2];
-      const double xc = L.nx[lj + 2][li + 1], yc = L.ny[lj + 2][li + 1];
-      const double xd = L.nx[lj + 2][li + 2], yd = L.ny[lj + 2][li + 2];
-      const double vol = B.xn ? 0.5 * fmad(xd - xa, yc - yb, -((xc - xb) * (yd - ya))) : B.vol;
       const double iv = M<double>::rcp(vol);
-      const long long ro = (long long)j * ni + i;
       if (B.src != nullptr) {  // the source part of Eq. (residual): - |Omega| S_h
 #pragma unroll
         for (int v = 0; v < 4; ++v) R[v] -= vol * ldg(B.src + v * ncell + ro);
@@ -482,15 +590,13 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
         double out[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          double un = 0.0;
-          if constexpr (SK::reads_un) un = L.un[v][lj][li];
           if constexpr (SK::low) {
-            out[v] = fmad(-f, R[v], un);
+            out[v] = fmad(-f, R[v], un[v]);
           } else {
             const double us = fmad(-f, R[v], qin[v]);
             if (MODE == 1) out[v] = us;
-            else if (MODE == 2) out[v] = fmad(0.75, un, 0.25 * us);
-            else out[v] = fmad(1.0 / 3.0, un, (2.0 / 3.0) * us);
+            else if (MODE == 2) out[v] = fmad(0.75, un[v], 0.25 * us);
+            else out[v] = fmad(1.0 / 3.0, un[v], (2.0 / 3.0) * us);
           }
           stg(B.u[bout] + v * ncell + ro, out[v]);
         }
@@ -501,26 +607,11 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
             nacc[v] = fmad(rv, rv, nacc[v]);
           }
         }
-        if constexpr (SK::cfl) {
-          double Sb[2][3];
-          if (B.xn) {
-            Sb[0][0] = 0.5 * ((yc - ya) + (yd - yb));
-            Sb[0][1] = -0.5 * ((xc - xa) + (xd - xb));
-            Sb[1][0] = -0.5 * ((yb - ya) + (yd - yc));
-            Sb[1][1] = 0.5 * ((xb - xa) + (xd - xc));
-          } else {
-            Sb[0][0] = B.area[0];
-            Sb[0][1] = 0.0;
-            Sb[1][0] = 0.0;
-            Sb[1][1] = B.area[1];
-          }
-          Sb[0][2] = Sb[1][2] = 0.0;
+        if constexpr (SK::cfl)
           dmin = fmin(dmin, mu > 0.0 ? cell_dt_limit_visc(out, Sb, vol, gamma, mu, I.prandtl, bad)
                                      : cell_dt_limit<2>(out, Sb, vol, gamma, bad));
-        }
       }
     }
-    __syncthreads();  // the LDS slab is reused by the next slab
   }
 
   // ---- per-tile partials: fixed-order wave reductions, then the four waves
