@@ -35,28 +35,26 @@ static bool graphs_enabled() {
 
 int launch_grid(const LaunchSet& s, int fp32, bool ns) {
   if (s.ntiles <= 0) return 0;
-  int cap;
+  int cap, per_wg = 1;  // workgroups that co-reside; tiles a workgroup takes at once
   if ((s.kind == kSet2D && ns) || s.kind == kSet2DNS) {
-    // one 256-thread workgroup per tile
     cap = fvrt::occupancy_blocks(fvk::stage2d_ns_kernel_ptr(fp32), 256);
-    cap = std::min(cap, s.ntiles);
   } else if (s.kind == kSet2D) {
     cap = fvrt::occupancy_blocks(fvk::stage2d_kernel_ptr(1, fp32), 256);
-    const int need = (s.ntiles + 3) / 4;
-    cap = std::min(cap, need);
+    per_wg = 4;
   } else if (s.kind == kSet3DG) {
     cap = fvrt::occupancy_blocks(fvk::stage3d_gen_kernel_ptr(fp32), 256);
-    cap = std::min(cap, s.ntiles);
   } else {
     const int ny = s.kind == kSet3D7 ? 7 : 3;
     cap = fvrt::occupancy_blocks(fvk::stage3d_kernel_ptr(1, fp32, ny), 64 * (ny + 1));
-    cap = std::min(cap, s.ntiles);
   }
   if (s.max_grid > 0) cap = std::min(cap, s.max_grid);
+  if (cap < fvk::kXcds) return std::max(1, std::min(cap, (s.ntiles + per_wg - 1) / per_wg));
   // a multiple of the XCD count, so that every XCD walks its own part of the
-  // tile list (see xcd_walk)
-  if (cap >= fvk::kXcds) cap -= cap % fvk::kXcds;
-  return std::max(cap, 1);
+  // tile list (see xcd_walk), and as many as the largest part has tiles for:
+  // rounded down, the few tiles left over run as a round of their own (324
+  // tiles on 320 workgroups took 195 us where 360 on 360 took 140)
+  const int chunk = (s.ntiles + fvk::kXcds - 1) / fvk::kXcds;
+  return std::min(cap - cap % fvk::kXcds, fvk::kXcds * ((chunk + per_wg - 1) / per_wg));
 }
 
 int enqueue_stage(const StepPlan& P, int mode, int fp32, double* rout, hipStream_t st) {
