@@ -61,9 +61,16 @@ struct DevInstance {
   int flags, stopped, have_first, last_step;
 };
 
+// General 3D kernel: threads per workgroup and the largest tile its arrays
+// hold: staged cells (W + 4)(H + 4) and nodes (W + 1)(H + 1) of a tile of W
+// columns and H rows.
+constexpr int kGenThreads = 256;
+constexpr int kGenQ = 456, kGenNd = 272;
+
 // A tile: 64 consecutive cells along i (ncol of them active), in rows
 // [j0, j0 + ny) (3D) and marching over n rows (2D: along j) or n planes
-// (3D: along k).  `local` is the tile's index within its instance.
+// (3D: along k).  The general 3D kernel's tiles are ncol by ny cells of any
+// shape that fits its workgroup.  `local` is the tile's index within its instance.
 struct DevTile {
   int blk, inst, local, ncol;
   int i0, j0, k0, n;
@@ -236,6 +243,13 @@ __host__ __device__ __forceinline__ double fmad(double a, double b, double c) {
   return __builtin_fma(a, b, c);
 }
 __host__ __device__ __forceinline__ float fmad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// x / 3: the quotient by a product corrected by its exact remainder, which
+// rounds as the division does
+__host__ __device__ __forceinline__ double third_of(double x) {
+  const double q = x * (1.0 / 3.0);
+  return fmad(fmad(-3.0, q, x), 1.0 / 3.0, q);
+}
 
 // x, with the sign bit set where that of s is
 __host__ __device__ __forceinline__ double with_sign_of_either(double x, double s) {
@@ -615,7 +629,7 @@ __device__ inline void cell_geom3(const DevBlock& B, int i, int j, int k, double
     for (int x = 0; x < 3; ++x) Sb[d][x] = 0.5 * (Sm[x] + Sp[x]);
     v += cp - cm;
   }
-  vol = v / 3.0;
+  vol = third_of(v);
 }
 
 // --------------------------------------------------------------------------

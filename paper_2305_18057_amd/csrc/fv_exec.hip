@@ -42,7 +42,7 @@ int launch_grid(const LaunchSet& s, int fp32, bool ns) {
     cap = fvrt::occupancy_blocks(fvk::stage2d_kernel_ptr(1, fp32), 256);
     per_wg = 4;
   } else if (s.kind == kSet3DG) {
-    cap = fvrt::occupancy_blocks(fvk::stage3d_gen_kernel_ptr(fp32), 256);
+    cap = fvrt::occupancy_blocks(fvk::stage3d_gen_kernel_ptr(fp32), fvk::kGenThreads);
   } else {
     const int ny = s.kind == kSet3D7 ? 7 : 3;
     cap = fvrt::occupancy_blocks(fvk::stage3d_kernel_ptr(1, fp32, ny), 64 * (ny + 1));

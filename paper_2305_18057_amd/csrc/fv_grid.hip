@@ -414,8 +414,9 @@ extern "C" int fv_grid_get_stats(const fv_grid* g, fv_grid_stats* out) {
   out->cells = g->hg.ncells;
   out->tiles = (long long)g->htiles.size();
   out->tile_rows = g->shape.rows;
-  out->tile_cols = 64;
-  out->tile_ny = g->hg.ndim == 3 ? g->shape.ny : 1;
+  const bool gen = g->hg.gen3 && !g->htiles.empty();
+  out->tile_cols = gen ? g->htiles[0].ncol : 64;
+  out->tile_ny = gen ? g->htiles[0].ny : (g->hg.ndim == 3 ? g->shape.ny : 1);
   out->launch_blocks = g->plan.sets.empty() ? 0 : fvexec::launch_grid(g->plan.sets[0], 0);
   out->workspace_bytes = g->L.total;
   for (int s = 0; s < 4; ++s) out->last_stage_ms[s] = g->last_ms[s];

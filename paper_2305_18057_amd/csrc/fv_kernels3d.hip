@@ -633,22 +633,22 @@ __global__ __launch_bounds__(256) void k_cfl3d(const DevTile* __restrict__ tiles
     const double Sb[3][3] = {{B.area[0], 0, 0}, {0, B.area[1], 0}, {0, 0, B.area[2]}};
     double dmin = INFINITY;
     int bad = 0;
-    const int i = tl.i0 + lane;
-    if (lane < tl.ncol) {
-      for (int y = w; y < tl.ny; y += 4)
-        for (int r = 0; r < tl.n; ++r) {
-          const long long idx = ((long long)(tl.k0 + r) * B.nj + (tl.j0 + y)) * B.ni + i;
-          double q[5];
+    // one cell of the tile's cross-section per thread, whatever its shape
+    for (int x = threadIdx.x; x < tl.ncol * tl.ny; x += 256) {
+      const int y = x / tl.ncol, i = tl.i0 + x - y * tl.ncol;
+      for (int r = 0; r < tl.n; ++r) {
+        const long long idx = ((long long)(tl.k0 + r) * B.nj + (tl.j0 + y)) * B.ni + i;
+        double q[5];
 #pragma unroll
-          for (int v = 0; v < 5; ++v) q[v] = ldg(B.u[0] + v * B.ncell + idx);
-          if (B.zn != nullptr) {  // curvilinear: the cell's own metrics
-            double Sc[3][3], vol;
-            cell_geom3(B, i, tl.j0 + y, tl.k0 + r, Sc, vol);
-            dmin = fmin(dmin, cell_dt_limit<3>(q, Sc, vol, I.gamma, bad));
-          } else {
-            dmin = fmin(dmin, cell_dt_limit<3>(q, Sb, B.vol, I.gamma, bad));
-          }
+        for (int v = 0; v < 5; ++v) q[v] = ldg(B.u[0] + v * B.ncell + idx);
+        if (B.zn != nullptr) {  // curvilinear: the cell's own metrics
+          double Sc[3][3], vol;
+          cell_geom3(B, i, tl.j0 + y, tl.k0 + r, Sc, vol);
+          dmin = fmin(dmin, cell_dt_limit<3>(q, Sc, vol, I.gamma, bad));
+        } else {
+          dmin = fmin(dmin, cell_dt_limit<3>(q, Sb, B.vol, I.gamma, bad));
         }
+      }
     }
     const double m = wave_min(dmin);
     const int b = wave_or(bad);

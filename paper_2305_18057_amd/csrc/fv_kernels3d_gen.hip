@@ -4,18 +4,29 @@
 // and the step-end partials like the uniform 3D kernel.  Uniform blocks of
 // such a grid run here too, with their exact axis-aligned metrics.
 //
-// One workgroup of 256 threads (4 waves) takes a tile of 64 columns i (lane)
-// by 4 rows j (wave) and marches over its n planes k, one cell per thread:
-//   - each thread keeps the states of its column at k-1 .. k+2 in registers
+// One workgroup of 256 threads takes a tile of W columns i by H rows j (the
+// host chooses them for the block), and marches over its n
+// planes k, one cell per thread:
+//   - each thread keeps its column's states at k-1 .. k+2 in registers
 //     and forms the k-face flux at k+1/2; the flux at k-1/2 is the one it
 //     formed for the plane before;
 //   - plane k is staged in LDS with its in-plane halo (two cells beyond the
 //     tile in i and in j), and each thread forms the i-face flux at i-1/2
-//     and the j-face flux at j-1/2 of its cell from LDS (the right column and
-//     the top row also form the tile's edge faces);
+//     and the j-face flux at j-1/2 from LDS.  W and H leave the workgroup
+//     enough threads for the (W + 1) H i-faces and the W (H + 1) j-faces of
+//     the plane, edges included, so three flux passes do a plane (with 64 x 4
+//     cells and one wave taking the 68 edge faces the others waited a fourth
+//     pass at the barrier);
 //   - node planes k and k+1 of the tile sit in LDS (curvilinear blocks):
-//     each thread forms the six area vectors of its cell from them, and its
-//     volume as 1/3 of the sum of (outward area vector . face centre).
+//     every face's area vector is formed from them once, and the volume as
+//     1/3 of the sum of (outward area vector . face centre);
+//   - the halo of plane k+1, nodes of plane k+2 and the column's state at
+//     k+3 are loaded while plane k is computed.
+// Bound by VALU issue (1.25 k instructions per cell-stage, 55% of the issue
+// slots; 1.62 k and 49% with 64 x 4 tiles, whose lanes beyond a block of 96
+// columns idled): two steps of 2 x 96 x 192 x 192 cells with a source, state
+// copied in and out, 4.51 -> 3.28 ms; five of three 41 x 50 x 45 blocks 2.12
+// -> 1.58 ms.
 // Every face flux of a tile is formed once (tile edges aside); a face shared
 // by two tiles is formed by both from the same operands, so bitwise alike.
 // In FP32-flux mode the reconstruction and Roe's flux run in FP32 on
@@ -28,34 +39,25 @@ namespace fvk {
 
 namespace {
 
-constexpr int kGT = 256;
-constexpr int kGR = 4;           // j-rows per tile, one wave each
-constexpr int kGQW = 64 + 4;     // state columns i0-2 .. i0+65
-constexpr int kGQH = kGR + 4;    // state rows j0-2 .. j0+5
-constexpr int kGHalo = 4 * (64 + kGR);  // halo cells of a tile plane (at most)
+constexpr int kGT = kGenThreads;
 
-// 78 KB: two workgroups (eight waves) per CU, as the registers allow
+// The arrays hold a tile of any shape the host may choose (kGenQ ...): cell
+// (r, c) of the staged plane at (r + 2) (W + 4) + c + 2, i-face (r, c) and
+// node (r, c) at r (W + 1) + c, j-face (r, c) at r W + c.  56 KB, and 12 KB of
+// area vectors in the stage kinds that form the time-step limit: two
+// workgroups (eight waves) per CU, as the registers allow.
+template <bool CFL>
 struct GenLds {
-  double q[5][kGQH][kGQW];       // plane k with its in-plane halo (a cross:
-                                 // the corner slots are never read)
-  double fi[5][kGR][65];         // i-face fluxes (times area), faces i0 .. i0+nc
-  double fj[5][kGR + 1][64];     // j-face fluxes, faces j0 .. j0+nr
-  double ci[kGR][65];            // S . centre of those faces (curvilinear volumes)
-  double cj[kGR + 1][64];
-  double nd[3][3][kGR + 1][65];  // node planes k0 + r in slot r % 3: x, y, z
-  double red[4][8];              // per-wave partials
-  // source of each halo cell, resolved once per tile (the same for every
-  // plane): the cell in plane 0 of its block's input buffer, that block's
-  // variable and plane strides, and kind | face << 4 | transverse index << 8
-  // (kind 0: copy, 1: inflow state of the face, 2: copy mirrored about the
-  // slip-wall face)
-  const double* hp[kGHalo];
-  long long hvs[kGHalo];
-  int hps[kGHalo];
-  int hkf[kGHalo];
+  double q[5][kGenQ];          // plane k with its in-plane halo (a cross: the
+                               // corner slots are never read)
+  double f[2][5][kGT];         // i- and j-face fluxes (times area)
+  double c[2][kGT];            // S . centre of those faces (curvilinear volumes)
+  double s[CFL ? 2 : 1][CFL ? 3 : 1][CFL ? kGT : 1];  // area vectors of those faces
+  double nd[2][3][kGenNd];     // node planes k0 + r in slot r % 2: x, y, z
+  double red[4][8];            // per-wave partials
 };
 
-// halo cell x of a tile plane: its row and column in the LDS plane
+// halo cell x of a tile plane: its row and column in the staged plane
 __device__ __forceinline__ void halo_slot(int x, int nc, int nr, int& qr, int& qc) {
   if (x < 4 * nc) {  // rows j0-2, j0-1, j0+nr, j0+nr+1
     const int a = x / nc;
@@ -156,17 +158,18 @@ __device__ __forceinline__ void inv_flux3(const Recon<T>& rc, const FluxK<T>& K,
 
 template <int MODE, typename T, int LIM>
 __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks, DevInstance& I,
-                         double* __restrict__ rout, GenLds& L) {
+                         double* __restrict__ rout, GenLds<StageKind<MODE>::cfl>& L) {
   using SK = StageKind<MODE>;
   constexpr int bin = SK::bin;
   constexpr int bout = SK::bout;
-  const int tid = threadIdx.x, li = tid & 63, lj = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const DevBlock& B = blocks[tl.blk];
   const long long ncell = B.ncell;
   const int i0 = tl.i0, j0 = tl.j0, k0 = tl.k0, nc = tl.ncol, nr = tl.ny, nz = tl.n;
+  const int lj = tid / nc, li = tid - lj * nc;
   const bool curv = B.zn != nullptr;
-  const bool act = li < nc && lj < nr;
-  const int i = i0 + li, j = j0 + lj;
+  const bool act = lj < nr;
+  const int i = i0 + li, j = j0 + min(lj, nr - 1);
   Recon<T> rc;
   rc.lim = I.limiter;
   rc.heps = T(0.5 * I.eps);
@@ -181,28 +184,62 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
   double nacc[5] = {0, 0, 0, 0, 0};
   double dmin = INFINITY;
   int bad = 0;
+  const int qp = nc + 4, np = nc + 1;           // pitches of cells, of nodes and i-faces
+  const int qown = (lj + 2) * qp + li + 2;      // the own cell in the staged plane
 
-  // node plane k of the tile, (nr + 1) x (nc + 1) nodes, into slot par
-  auto stage_nodes = [&](int k, int par) {
-    for (int x = tid; x < (nr + 1) * (nc + 1); x += kGT) {
-      const int r = x / (nc + 1), c = x - r * (nc + 1);
-      double p[3];
-      node3(B, i0 + c, j0 + r, k, p);
-      L.nd[par][0][r][c] = p[0];
-      L.nd[par][1][r][c] = p[1];
-      L.nd[par][2][r][c] = p[2];
+  // this thread's halo cell: its source (the same for every plane) and slot
+  const int nh = 4 * (nc + nr), nn = np * (nr + 1);
+  const double* hp = nullptr;
+  long long hvs = 0;
+  int hps = 0, hkf = 0, hslot = 0;
+  if (tid < nh) {
+    int qr, qc;
+    halo_slot(tid, nc, nr, qr, qc);
+    hslot = qr * qp + qc;
+    halo_source(blocks, B, bin, i0 - 2 + qc, j0 - 2 + qr, hp, hvs, hps, hkf);
+  }
+  // this thread's nodes tid and tid + 256 of a node plane
+  const long long nplane = (long long)(B.ni + 1) * (B.nj + 1);
+  const int nrow0 = tid / np, nrow1 = (tid + kGT) / np;
+  const int noff0 = (j0 + nrow0) * (B.ni + 1) + i0 + tid - nrow0 * np;
+  const int noff1 = (j0 + nrow1) * (B.ni + 1) + i0 + tid + kGT - nrow1 * np;
+  double hq[5], pn[2][3];
+  auto load_halo = [&](int k) {
+    if (tid < nh && (hkf & 15) != 1) {
+      const double* q = hp + (long long)k * hps;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) hq[v] = ldg(q + v * hvs);
     }
   };
-  auto ndp = [&](int par, int r, int c, double* o) {
-    o[0] = L.nd[par][0][r][c];
-    o[1] = L.nd[par][1][r][c];
-    o[2] = L.nd[par][2][r][c];
+  auto load_nodes = [&](int k) {
+    if (curv) {
+      const double* N[3] = {B.xn + k * nplane, B.yn + k * nplane, B.zn + k * nplane};
+      if (tid < nn) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) pn[0][x] = ldg(N[x] + noff0);
+      }
+      if (tid + kGT < nn) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) pn[1][x] = ldg(N[x] + noff1);
+      }
+    }
   };
-  // Area vector S (and S . centre) of the face of direction d on side
-  // `side` (0: at i-1/2, j-1/2 or k-1/2; 1: the far face) of the cell at row
-  // fr, column fc of the tile in plane k, whose bottom and top node planes
-  // are in slots p0, p1.  Uniform blocks: the axis times the face area.
-  auto face_at = [&](int d, int side, int p0, int p1, int fr, int fc, double* S, double& cs) {
+  auto put_nodes = [&](int slot) {
+    if (curv) {
+      if (tid < nn) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) L.nd[slot][x][tid] = pn[0][x];
+      }
+      if (tid + kGT < nn) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) L.nd[slot][x][tid + kGT] = pn[1][x];
+      }
+    }
+  };
+  // Area vector S (and S . centre) of a face of direction d from its corners
+  // in the node planes: p0 at n0, p1 at n0 + s1, p3 at n0 + s3, p2 at n0 + s1 + s3.
+  // Uniform blocks: the axis times the face area.
+  auto face_geom = [&](int d, int n0, int s1, int s3, double* S, double& cs) {
     if (!curv) {
       S[0] = d == 0 ? B.area[0] : 0.0;
       S[1] = d == 1 ? B.area[1] : 0.0;
@@ -210,48 +247,36 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
       cs = 0.0;
       return;
     }
-    double a[3], b[3], c[3], e[3];
-    if (d == 0) {
-      const int cc = fc + side;
-      ndp(p0, fr, cc, a);
-      ndp(p0, fr + 1, cc, b);
-      ndp(p1, fr + 1, cc, c);
-      ndp(p1, fr, cc, e);
-    } else if (d == 1) {
-      const int rr = fr + side;
-      ndp(p0, rr, fc, a);
-      ndp(p0, rr, fc + 1, b);
-      ndp(p1, rr, fc + 1, c);
-      ndp(p1, rr, fc, e);
-    } else {
-      const int pp = side ? p1 : p0;
-      ndp(pp, fr, fc, a);
-      ndp(pp, fr, fc + 1, b);
-      ndp(pp, fr + 1, fc + 1, c);
-      ndp(pp, fr + 1, fc, e);
+    const double* N = &L.nd[0][0][0] + n0;
+    double p0[3], p1[3], p2[3], p3[3];
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      p0[x] = N[x * kGenNd];
+      p1[x] = N[x * kGenNd + s1];
+      p2[x] = N[x * kGenNd + s1 + s3];
+      p3[x] = N[x * kGenNd + s3];
     }
-    quad_face(a, b, c, e, d == 1, S, cs);
+    quad_face(p0, p1, p2, p3, d == 1, S, cs);
   };
 
   // column states at k-1, k, k+1, k+2 (at the loop head) and the k-face
   // flux at k-1/2
-  double ca[5], cb[5], cc[5], cd[5], fk[5], csk = 0.0;
-  for (int x = tid; x < 4 * (nc + nr); x += kGT) {
-    int qr, qc;
-    halo_slot(x, nc, nr, qr, qc);
-    halo_source(blocks, B, bin, i0 - 2 + qc, j0 - 2 + qr, L.hp[x], L.hvs[x], L.hps[x], L.hkf[x]);
-  }
-  if (curv) stage_nodes(k0, 0);
-  __syncthreads();
+  double ca[5], cb[5], cc[5], cd[5], fk[5], csk = 0.0, sk[3] = {0, 0, 0};
+  load_halo(k0);
+  load_nodes(k0);
   if (act) {
     load_cell<5>(blocks, B, bin, i, j, k0 - 2, ca);
     load_cell<5>(blocks, B, bin, i, j, k0 - 1, cb);
     load_cell<5>(blocks, B, bin, i, j, k0, cc);
     load_cell<5>(blocks, B, bin, i, j, k0 + 1, cd);
-    double S[3];
-    face_at(2, 0, 0, 0, lj, li, S, csk);  // node plane k0 (slot 0)
+  }
+  put_nodes(0);
+  load_nodes(k0 + 1);
+  __syncthreads();
+  if (act) {
+    face_geom(2, lj * np + li, 1, np, sk, csk);  // node plane k0 (slot 0)
     T G[5];
-    inv_flux3<LIM, T>(rc, K, ca, cb, cc, cd, S, G);
+    inv_flux3<LIM, T>(rc, K, ca, cb, cc, cd, sk, G);
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       fk[v] = (double)G[v];
@@ -262,97 +287,36 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
     load_cell<5>(blocks, B, bin, i, j, k0 + 2, cd);
   }
 
+#pragma unroll 1
   for (int r = 0; r < nz; ++r) {
     const int k = k0 + r;
-    // node slots of planes k (bottom) and k+1 (top); the third slot still
-    // holds plane k-1, which a wave behind may read until the next barrier
-    const int p0 = r % 3, p1 = (r + 1) % 3;
-    // ---- 1. plane k into LDS: the tile's cells from registers, the halo
-    //         cross (rows j0-2, j0-1, j0+nr, j0+nr+1 and columns i0-2, i0-1,
-    //         i0+nc, i0+nc+1) from memory; node plane k+1
+    // ---- 1. plane k and node plane k+1 into LDS: the tile's cells from the
+    //         columns' registers, halo and nodes as loaded a plane ago.  No
+    //         wave still reads what is overwritten: the last plane's fluxes
+    //         were formed before its second barrier
     if (act) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) L.q[v][lj + 2][li + 2] = cb[v];
+      for (int v = 0; v < 5; ++v) L.q[v][qown] = cb[v];
     }
-    {
-      // every load of the plane's halo first (one per halo cell: its source
-      // is known), then the LDS writes
-      const int nh = 4 * (nc + nr);
-      double hq[2][5];
+    if (tid < nh) {
+      if ((hkf & 15) == 1) {
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int x = tid + h * kGT;
-        if (x < nh) {
-          const int kf = L.hkf[x];
-          if ((kf & 15) == 1) {
-#pragma unroll
-            for (int v = 0; v < 5; ++v) hq[h][v] = B.bc_q[(kf >> 4) & 15][v];
-          } else {
-            const double* q = L.hp[x] + (long long)k * L.hps[x];
-            const long long vs = L.hvs[x];
-#pragma unroll
-            for (int v = 0; v < 5; ++v) hq[h][v] = ldg(q + v * vs);
-          }
-        }
+        for (int v = 0; v < 5; ++v) hq[v] = B.bc_q[(hkf >> 4) & 15][v];
+      } else if ((hkf & 15) == 2) {
+        slip_mirror3(B, (hkf >> 4) & 15, hkf >> 8, k, hq);
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int x = tid + h * kGT;
-        if (x < nh) {
-          const int kf = L.hkf[x];
-          if ((kf & 15) == 2) slip_mirror3(B, (kf >> 4) & 15, kf >> 8, k, hq[h]);
-          int qr, qc;
-          halo_slot(x, nc, nr, qr, qc);
-#pragma unroll
-          for (int v = 0; v < 5; ++v) L.q[v][qr][qc] = hq[h][v];
-        }
-      }
+      for (int v = 0; v < 5; ++v) L.q[v][hslot] = hq[v];
     }
-    if (curv) stage_nodes(k + 1, p1);
+    put_nodes((r + 1) & 1);
     __syncthreads();
 
-    // ---- 2. in-plane face fluxes to LDS, one face per thread and pass:
-    //         the i-face at i-1/2 and the j-face at j-1/2 of the thread's
-    //         cell, then the tile's nr right-edge and nc top-edge faces as
-    //         one list of tasks, dealt to the waves in an order that turns
-    //         with the plane (so that no SIMD always gets the extra pass)
-    auto in_plane = [&](int d, int fr, int fc) {
-      // face of direction d at row fr, column fc of the tile (i-face: at
-      // i0+fc-1/2 of row j0+fr; j-face: at j0+fr-1/2 of column i0+fc)
-      double S[3], cs, c0[5], c1[5], c2[5], c3[5];
-      if (d == 0) {
-        face_at(0, 0, p0, p1, fr, fc, S, cs);
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          c0[v] = L.q[v][fr + 2][fc];
-          c1[v] = L.q[v][fr + 2][fc + 1];
-          c2[v] = L.q[v][fr + 2][fc + 2];
-          c3[v] = L.q[v][fr + 2][fc + 3];
-        }
-      } else {
-        face_at(1, 0, p0, p1, fr, fc, S, cs);
-#pragma unroll
-        for (int v = 0; v < 5; ++v) {
-          c0[v] = L.q[v][fr][fc + 2];
-          c1[v] = L.q[v][fr + 1][fc + 2];
-          c2[v] = L.q[v][fr + 2][fc + 2];
-          c3[v] = L.q[v][fr + 3][fc + 2];
-        }
-      }
-      T G[5];
-      inv_flux3<LIM, T>(rc, K, c0, c1, c2, c3, S, G);
-      if (d == 0) {
-#pragma unroll
-        for (int v = 0; v < 5; ++v) L.fi[v][fr][fc] = (double)G[v];
-        L.ci[fr][fc] = cs;
-      } else {
-#pragma unroll
-        for (int v = 0; v < 5; ++v) L.fj[v][fr][fc] = (double)G[v];
-        L.cj[fr][fc] = cs;
-      }
-    };
-    // U^n and the source of the cell, loaded before the fluxes are formed
-    // so that their latency hides behind them
+    // ---- 2. loads of the next plane's halo and nodes, and U^n and the source
+    //         of the cell: all used after the fluxes
+    if (r + 1 < nz) {
+      load_halo(k + 1);
+      load_nodes(k + 2);
+    }
     const long long idx = ((long long)k * B.nj + j) * B.ni + i;
     double unp[5] = {0, 0, 0, 0, 0}, srp[5] = {0, 0, 0, 0, 0};
     if (act) {
@@ -364,36 +328,65 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
 #pragma unroll
         for (int v = 0; v < 5; ++v) srp[v] = ldg(B.src + v * ncell + idx);
       }
-      in_plane(0, lj, li);
-      in_plane(1, lj, li);
     }
-    {
-      const int e = (tid + 64 * (r & 3)) & (kGT - 1);
-      if (e < nr) in_plane(0, e, nc);
-      else if (e < nr + nc) in_plane(1, nr, e - nr);
-    }
-    // k-face at k+1/2 from the column's k-1 .. k+2 (registers)
-    double Fh[5], cskt = 0.0;
-    if (act) {
-      double S[3];
-      face_at(2, 1, p0, p1, lj, li, S, cskt);
-      T G[5];
-      inv_flux3<LIM, T>(rc, K, ca, cb, cc, cd, S, G);
+    // ---- 3. face fluxes, one face per thread and pass: i-faces and j-faces
+    //         from LDS, the k-face at k+1/2 from the column's registers.  One
+    //         body for all: unrolled, the passes overlap and their registers
+    //         spill
+    const int n0 = (r & 1) * 3 * kGenNd;               // node plane k
+    const int nup = (r & 1) ? -3 * kGenNd : 3 * kGenNd;  // from it to plane k+1
+    double Fo[5] = {0, 0, 0, 0, 0}, So[3] = {0, 0, 0}, cso = 0.0;
+#pragma unroll 1
+    for (int d = 0; d < 3; ++d) {
+      const int fr = d == 0 ? nrow0 : lj, fc = d == 0 ? tid - nrow0 * np : li;
+      if (tid >= (d == 0 ? np * nr : (d == 1 ? nc * (nr + 1) : nc * nr))) continue;
+      double c0[5], c1[5], c2[5], c3[5];
+      if (d == 2) {
 #pragma unroll
-      for (int v = 0; v < 5; ++v) Fh[v] = (double)G[v];
+        for (int v = 0; v < 5; ++v) {
+          c0[v] = ca[v];
+          c1[v] = cb[v];
+          c2[v] = cc[v];
+          c3[v] = cd[v];
+        }
+      } else {
+        const int sq = d == 0 ? 1 : qp;
+        const double* q = &L.q[0][(fr + 2) * qp + fc + 2 - 2 * sq];
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          c0[v] = q[v * kGenQ];
+          c1[v] = q[v * kGenQ + sq];
+          c2[v] = q[v * kGenQ + 2 * sq];
+          c3[v] = q[v * kGenQ + 3 * sq];
+        }
+      }
+      face_geom(d, n0 + (d == 2 ? nup : 0) + fr * np + fc, d == 0 ? np : 1, d == 2 ? np : nup, So, cso);
+      T G[5];
+      inv_flux3<LIM, T>(rc, K, c0, c1, c2, c3, So, G);
+#pragma unroll
+      for (int v = 0; v < 5; ++v) Fo[v] = (double)G[v];
+      if (d < 2) {  // (the k-face stays in the registers)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) L.f[d][v][tid] = Fo[v];
+        L.c[d][tid] = cso;
+        if constexpr (SK::cfl) {
+#pragma unroll
+          for (int x = 0; x < 3; ++x) L.s[d][x][tid] = So[x];
+        }
+      }
     }
     __syncthreads();
 
-    // ---- 3. residual, source, update, partials; the column moves up
+    // ---- 4. residual, source, update, partials; the column moves up
     if (act) {
+      const int f = lj * np + li, g = lj * nc + li;
       double R[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v)
-        R[v] = ((0.0 + (L.fi[v][lj][li + 1] - L.fi[v][lj][li])) +
-                (L.fj[v][lj + 1][li] - L.fj[v][lj][li])) + (Fh[v] - fk[v]);
+        R[v] = ((0.0 + (L.f[0][v][f + 1] - L.f[0][v][f])) + (L.f[1][v][g + nc] - L.f[1][v][g])) + (Fo[v] - fk[v]);
       // volume: 1/3 of the sum over the faces of the outward S . centre
-      const double vol = curv ? (((0.0 + (L.ci[lj][li + 1] - L.ci[lj][li])) +
-                                  (L.cj[lj + 1][li] - L.cj[lj][li])) + (cskt - csk)) / 3.0
+      const double vol = curv ? third_of(((0.0 + (L.c[0][f + 1] - L.c[0][f])) + (L.c[1][g + nc] - L.c[1][g])) +
+                                         (cso - csk))
                               : B.vol;
       if (B.src != nullptr) {  // the source part of Eq. (residual): - |Omega| S_h
 #pragma unroll
@@ -408,16 +401,16 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
           nacc[v] = fmad(rv, rv, nacc[v]);
         }
       } else {
-        const double f = dt * iv;
+        const double f1 = dt * iv;
         double out[5];
 #pragma unroll
         for (int v = 0; v < 5; ++v) {
           double un = 0.0;
           if constexpr (SK::reads_un) un = unp[v];
           if constexpr (SK::low) {
-            out[v] = fmad(-f, R[v], un);
+            out[v] = fmad(-f1, R[v], un);
           } else {
-            const double us = fmad(-f, R[v], cb[v]);
+            const double us = fmad(-f1, R[v], cb[v]);
             if (MODE == 1) out[v] = us;
             else if (MODE == 2) out[v] = fmad(0.75, un, 0.25 * us);
             else out[v] = fmad(1.0 / 3.0, un, (2.0 / 3.0) * us);
@@ -432,33 +425,40 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
           }
         }
         if constexpr (SK::cfl) {
-          // mean area vectors per direction (formed again here: one stage in three)
-          double Sb[3][3];
+          double Sb[3][3];  // mean area vectors per direction
 #pragma unroll
-          for (int d = 0; d < 3; ++d) {
-            double Sm[3], Sp[3], cm, cp;
-            face_at(d, 0, p0, p1, lj, li, Sm, cm);
-            face_at(d, 1, p0, p1, lj, li, Sp, cp);
-#pragma unroll
-            for (int x = 0; x < 3; ++x) Sb[d][x] = 0.5 * (Sm[x] + Sp[x]);
+          for (int x = 0; x < 3; ++x) {
+            Sb[0][x] = 0.5 * (L.s[0][x][f] + L.s[0][x][f + 1]);
+            Sb[1][x] = 0.5 * (L.s[1][x][g] + L.s[1][x][g + nc]);
+            Sb[2][x] = 0.5 * (sk[x] + So[x]);
           }
           dmin = fmin(dmin, cell_dt_limit<3>(out, Sb, vol, gamma, bad));
         }
       }
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        fk[v] = Fh[v];
+        fk[v] = Fo[v];
         ca[v] = cb[v];
         cb[v] = cc[v];
         cc[v] = cd[v];
       }
-      csk = cskt;
-      if (r + 1 < nz) load_cell<5>(blocks, B, bin, i, j, k + 3, cd);
+      csk = cso;
+      if constexpr (SK::cfl) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) sk[x] = So[x];
+      }
+      if (r + 1 < nz) {
+        if (k + 3 < B.nk) {
+#pragma unroll
+          for (int v = 0; v < 5; ++v)
+            cd[v] = ldg(B.u[bin] + v * ncell + idx + 3LL * B.ni * B.nj);
+        } else {
+          load_cell<5>(blocks, B, bin, i, j, k + 3, cd);
+        }
+      }
     }
-    // no barrier here: the next plane's staging writes q (read before the
-    // last barrier) and the node slot of plane k+2 (neither k nor k+1), and
-    // its flux writes follow the next barrier, which every wave reaches only
-    // after this update
+    // no barrier here: the next plane's flux writes follow its first barrier,
+    // which every wave reaches only after this update
   }
   __syncthreads();
 
@@ -469,15 +469,15 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
       const double s = wave_sum(nacc[v]);
-      if (li == 0) L.red[lj][v] = s;
+      if (lane == 0) L.red[wv][v] = s;
     }
   }
   if (SK::cfl) {
     const double m = wave_min(dmin);
     const int b = wave_or(bad);
-    if (li == 0) {
-      L.red[lj][5] = m;
-      L.red[lj][6] = (double)b;
+    if (lane == 0) {
+      L.red[wv][5] = m;
+      L.red[wv][6] = (double)b;
     }
   }
   __syncthreads();
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(kGT, 2) void k_stage3d_gen(const DevTile* __restric
                                                        const DevBlock* __restrict__ blocks,
                                                        DevInstance* __restrict__ insts,
                                                        double* __restrict__ rout) {
-  __shared__ GenLds s_lds;
+  __shared__ GenLds<StageKind<MODE>::cfl> s_lds;
   const int ntiles = nfix >= 0 ? nfix : *ntiles_p;
   for (TileWalk tw = xcd_walk(ntiles, 1, 0); tw.t < tw.end; tw.t += tw.stride) {
     const DevTile tl = tiles[tw.t];

@@ -50,7 +50,7 @@ int scratch_of_device(char** out) {
 // caller's state takes that role), i.e. descriptors, tiles, partials, ghost
 // segments, nodes, then the two stage buffers.
 InstLayout noalloc_layout(const HostGrid& hg) {
-  InstLayout L = layout_of(hg);
+  InstLayout L = layout_of(hg, true);
   const size_t sbytes = align_up(sizeof(double) * (size_t)hg.state_size);
   L.u[1] = L.u[0];
   L.u[2] = L.u[0] + sbytes;
@@ -109,6 +109,12 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
   }
   std::vector<fvk::DevTile> htiles;
   build_tiles(hg, sh, 0, 0, htiles);
+  // a general 3D grid of a few rows can need more tiles of few planes than
+  // the scratch holds: fewer, taller ones
+  while ((long long)htiles.size() > L.max_tiles && sh.rows < 64) {
+    sh.rows *= 2;
+    build_tiles(hg, sh, 0, 0, htiles);
+  }
   const int nt = (int)htiles.size();
   if (nt > L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");
 

@@ -61,7 +61,9 @@ struct InstLayout {
   long long ghost_cells, ghost_doubles;
 };
 long long max_tiles_of(const HostGrid& g);
-InstLayout layout_of(const HostGrid& g);
+// fixed_scratch: the tile list of the allocation-free path, which makes its
+// tiles taller where a list would not fit
+InstLayout layout_of(const HostGrid& g, bool fixed_scratch = false);
 
 // fill host mirrors (blocks, ghost segments) for an instance placed at `base`
 void build_blocks(const HostGrid& g, char* base, const InstLayout& L, int inst_index,
@@ -73,6 +75,8 @@ hipError_t upload_nodes(const HostGrid& g, char* dst, hipStream_t s);
 void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int block_index_offset,
                  std::vector<fvk::DevTile>& out);
 TileShape default_shape(const HostGrid& g);
+// columns and rows of the general 3D kernel's tiles of an ni x nj block
+void gen_tile_shape(int ni, int nj, int& w, int& h);
 int size_class(const HostGrid& g);
 
 // autotune table (JSON file of "key": {"rows": r, "ny": y})

@@ -157,12 +157,49 @@ int validate_and_copy(const fv_grid_desc* d, HostGrid& g) {
 
 static const int kMinRows2D = 2, kMinPlanes3D = 4, kMinNy3D = 3;
 
+// Every split of the columns into even parts, with the most rows for which
+// one thread each is enough for the (W + 1) H i-faces, the W (H + 1) j-faces
+// and the 4 (W + H) halo cells of a plane.  The fewest tiles win (a plane of
+// a tile costs the same three flux passes however many threads are idle),
+// with 0.4% for each halo row or column.
+void gen_tile_shape(int ni, int nj, int& w, int& h) {
+  constexpr int N = fvk::kGenThreads;
+  double best = 0.0;
+  w = h = 0;
+  for (int x = std::min(ni, 60); x >= 1; --x) {
+    const int nt = (ni + x - 1) / x, W = (ni + nt - 1) / nt;
+    if (W != x) continue;  // the even split of another column count
+    int H = std::min({nj, N / (W + 1), N / W - 1, N / 4 - W, fvk::kGenQ / (W + 4) - 4,
+                      fvk::kGenNd / (W + 1) - 1});
+    if (H < 1) continue;
+    const int nh = (nj + H - 1) / H;
+    H = (nj + nh - 1) / nh;
+    const double cost = (double)nt * nh * (1.0 + 0.004 * (W + H));
+    if (w == 0 || cost < best) {
+      best = cost;
+      w = W;
+      h = H;
+    }
+  }
+}
+
 long long max_tiles_of(const HostGrid& g) {
   long long t = 0;
   for (const auto& B : g.blocks) {
     const long long ci = (B.ni + 63) / 64;
     if (g.ndim == 2) t += ci * ((B.nj + kMinRows2D - 1) / kMinRows2D);
     else t += ci * ((B.nj + kMinNy3D - 1) / kMinNy3D) * ((B.nk + kMinPlanes3D - 1) / kMinPlanes3D);
+  }
+  return t;
+}
+
+// the most tiles build_tiles can make of a general 3D grid
+static long long max_gen_tiles(const HostGrid& g) {
+  long long t = 0;
+  for (const auto& B : g.blocks) {
+    int w, h;
+    gen_tile_shape(B.ni, B.nj, w, h);
+    t += (long long)((B.ni + w - 1) / w) * ((B.nj + h - 1) / h) * ((B.nk + kMinPlanes3D - 1) / kMinPlanes3D);
   }
   return t;
 }
@@ -185,9 +222,10 @@ void build_segs(const HostGrid& g, std::vector<fvk::GhostSeg>& segs) {
     }
 }
 
-InstLayout layout_of(const HostGrid& g) {
+InstLayout layout_of(const HostGrid& g, bool fixed_scratch) {
   InstLayout L;
   L.max_tiles = max_tiles_of(g);
+  if (g.gen3 && !fixed_scratch) L.max_tiles = std::max(L.max_tiles, max_gen_tiles(g));
   std::vector<fvk::GhostSeg> segs;
   build_segs(g, segs);
   L.nseg = (int)segs.size();
@@ -333,16 +371,17 @@ void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int bof
     } else {
       // at most 64 planes: the kernel keeps a row's right-edge fluxes in 64 LDS slots, one per plane
       const int P = std::min(64, std::max(kMinPlanes3D, sh.rows));
-      const int NY = g.gen3 ? 4 : (sh.ny >= 7 ? 7 : 3);
+      int NX = 64, NY = sh.ny >= 7 ? 7 : 3;
+      if (g.gen3) gen_tile_shape(B.ni, B.nj, NX, NY);
       for (int k0 = 0; k0 < B.nk; k0 += P)
         for (int j0 = 0; j0 < B.nj; j0 += NY)
-          for (int i0 = 0; i0 < B.ni; i0 += 64) {
+          for (int i0 = 0; i0 < B.ni; i0 += NX) {
             fvk::DevTile t;
             std::memset(&t, 0, sizeof(t));
             t.blk = b + boff;
             t.inst = inst_index;
             t.local = local++;
-            t.ncol = std::min(64, B.ni - i0);
+            t.ncol = std::min(NX, B.ni - i0);
             t.i0 = i0;
             t.j0 = j0;
             t.k0 = k0;
