@@ -10,31 +10,44 @@ using namespace fvrt;
 
 namespace fvgrid {
 
+// the tile list of the Navier-Stokes (ns) or the Euler kernel for the coming
+// launches.  The instance's tile count sizes its partials (value-major) and
+// their reductions: it follows the list with the next put_inst
+static void use_list(fv_grid* g, bool ns) {
+  g->list = ns && g->hg.two_lists() ? 1 : 0;
+  fvexec::LaunchSet& ls = g->plan.sets[0];
+  ls.tiles = g->d_tiles[g->list];
+  ls.ntiles_dev = g->d_ntiles + g->list;
+  ls.ntiles = (int)g->htiles[g->list].size();
+  ls.kind = fvexec::set_kind(g->hg.ndim, g->hg.gen3, g->shape[g->list].ny);
+  g->plan.ns = ns;
+  g->hinst.ntiles = ls.ntiles;
+}
+
 int upload_tiles(fv_grid* g) {
-  build_tiles(g->hg, g->shape, 0, 0, g->htiles);
-  const int nt = (int)g->htiles.size();
-  if (nt > g->L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");
-  FV_HIP(hipMemcpyAsync(g->d_tiles, g->htiles.data(), sizeof(fvk::DevTile) * nt,
-                        hipMemcpyHostToDevice, g->stream));
-  FV_HIP(hipMemcpyAsync(g->d_ntiles, &nt, sizeof(int), hipMemcpyHostToDevice, g->stream));
-  // the instance's tile count sizes its partials (value-major) and their
-  // reductions: it follows the tile list at once, on the host and the device
-  g->hinst.ntiles = nt;
-  FV_HIP(hipMemcpyAsync((char*)g->d_inst + offsetof(fvk::DevInstance, ntiles), &g->hinst.ntiles,
-                        sizeof(int), hipMemcpyHostToDevice, g->stream));
+  const int lists = g->hg.two_lists() ? 2 : 1;
+  int nt[2] = {0, 0};
+  for (int x = 0; x < lists; ++x) {
+    build_tiles(g->hg, g->shape[x], 0, 0, g->htiles[x]);
+    nt[x] = (int)g->htiles[x].size();
+    if (nt[x] > g->L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");
+    FV_HIP(hipMemcpyAsync(g->d_tiles[x], g->htiles[x].data(), sizeof(fvk::DevTile) * nt[x],
+                          hipMemcpyHostToDevice, g->stream));
+  }
+  FV_HIP(hipMemcpyAsync(g->d_ntiles, nt, sizeof(nt), hipMemcpyHostToDevice, g->stream));
+  const bool ns = g->plan.ns;
   g->plan = fvexec::StepPlan();
   g->plan.blocks = g->d_blocks;
   g->plan.insts = g->d_inst;
   g->plan.active = nullptr;
   g->plan.ninst = 1;
   fvexec::LaunchSet ls;
-  ls.tiles = g->d_tiles;
-  ls.ntiles_dev = g->d_ntiles;
-  ls.ntiles = nt;
   // graphs are captured again after every change of the tile list (below)
   ls.count_fixed = true;
-  ls.kind = fvexec::set_kind(g->hg.ndim, g->hg.gen3, g->shape.ny);
   g->plan.sets.push_back(ls);
+  use_list(g, ns);
+  FV_HIP(hipMemcpyAsync((char*)g->d_inst + offsetof(fvk::DevInstance, ntiles), &g->hinst.ntiles,
+                        sizeof(int), hipMemcpyHostToDevice, g->stream));
   g->graphs.clear();
   // the tile list and the instance's tile count must be on the device before
   // the next launch; the caller's stream orders that
@@ -83,15 +96,17 @@ bool ns_kernel(const HostGrid& hg, const fv_params* p) {
 }
 
 // The stage kernels these parameters take: a viscosity or a no-slip face
-// needs the Navier-Stokes kernel (2D grids).  Called after the parameters
-// are on the device; when the viscosity differs from the one the current
-// time-step bound was formed with, the bound is formed again.
+// needs the Navier-Stokes kernel (2D grids).  hinst holds the parameters; when
+// the viscosity differs from the one the current time-step bound was formed
+// with, the bound is formed again.
 int use_params(fv_grid* g, const fv_params* p) {
+  use_list(g, ns_kernel(g->hg, p));
+  int st = put_inst(g, false);
+  if (st) return st;
   if (p->mu > 0.0 && g->hg.ndim != 2)
     return set_error(FV_E_UNSUPPORTED, "the viscous flux is provided for 2D grids only");
-  g->plan.ns = ns_kernel(g->hg, p);
   if (g->have_state && (g->hinst.mu != g->cfl_mu || g->hinst.prandtl != g->cfl_pr)) {
-    const int st = cfl_pass(g);
+    st = cfl_pass(g);
     if (st) return st;
   }
   return FV_OK;
@@ -140,7 +155,8 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
   g->d_blocks = (fvk::DevBlock*)(g->ws + g->L.blocks);
   g->d_inst = (fvk::DevInstance*)(g->ws + g->L.inst);
   g->d_ntiles = (int*)(g->ws + g->L.ntiles);
-  g->d_tiles = (fvk::DevTile*)(g->ws + g->L.tiles);
+  g->d_tiles[0] = (fvk::DevTile*)(g->ws + g->L.tiles);
+  g->d_tiles[1] = (fvk::DevTile*)(g->ws + g->L.tiles_ns);
   g->d_part = (double*)(g->ws + g->L.part);
   g->d_segs = (fvk::GhostSeg*)(g->ws + g->L.segs);
   for (int s = 0; s < 3; ++s) g->d_u[s] = (double*)(g->ws + g->L.u[s]);
@@ -181,11 +197,15 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
   g->hinst.stopped = 1;
   g->hinst.flags = fvk::FLAG_NONPHYS;  // no state yet
   // tile shape: autotune table for this size class, else the default
-  TileShape sh = default_shape(g->hg);
   const char* tp = tune_path(nullptr);
   TileShape tsh;
-  if (tune_lookup(tp, tune_key(g->hg, FV_FP64), tsh)) sh = tsh;
-  g->shape = sh;
+  if (tune_lookup(tp, tune_key(g->hg, FV_FP64), tsh)) {
+    g->shape[0] = g->shape[1] = tsh;
+  } else {
+    g->shape[0] = default_shape(g->hg, g->hg.ndim == 2 && !g->hg.two_lists());
+    g->shape[1] = default_shape(g->hg, g->hg.ndim == 2);
+  }
+  g->plan.ns = g->hg.ndim == 2 && !g->hg.two_lists();
   st = fvgrid::upload_tiles(g);
   if (st) return fail(st);
   st = fvgrid::put_inst(g, true);
@@ -257,8 +277,6 @@ extern "C" int fv_residual(fv_grid* g, const fv_params* p, double* R, int on_dev
   if (st) return st;
   if (!g->have_state) return set_error(FV_E_INVAL, "no state set");
   params_to_inst(p, g->hg.gamma, g->hinst);
-  st = put_inst(g, false);
-  if (st) return st;
   if ((st = use_params(g, p))) return st;
   double* dst = (R && on_device) ? R : g->d_u[1];
   g->plan.lim = p->limiter;
@@ -305,8 +323,6 @@ static int run_steps(fv_grid* g, const fv_params* p, long long nsteps, double dr
   params_to_inst(p, g->hg.gamma, g->hinst);
   g->hinst.drop_tol = drop_tol;
   g->hinst.step_limit = g->hinst.steps + nsteps;
-  st = put_inst(g, false);
-  if (st) return st;
   if ((st = use_params(g, p))) return st;
   FV_HIP(fvk::launch_prepare(g->stream, g->d_inst, nullptr, 1));
   const int fp32 = p->precision == FV_FP32_FLUX;
@@ -354,8 +370,6 @@ extern "C" int fv_step_timed(fv_grid* g, const fv_params* p, int nsteps, fv_step
   params_to_inst(p, g->hg.gamma, g->hinst);
   g->hinst.drop_tol = 0.0;
   g->hinst.step_limit = g->hinst.steps + nsteps;
-  st = put_inst(g, false);
-  if (st) return st;
   if ((st = use_params(g, p))) return st;
   FV_HIP(fvk::launch_prepare(g->stream, g->d_inst, nullptr, 1));
   const int fp32 = p->precision == FV_FP32_FLUX;
@@ -412,12 +426,13 @@ extern "C" int fv_grid_get_stats(const fv_grid* g, fv_grid_stats* out) {
   if (!g || !out) return set_error(FV_E_INVAL, "null argument");
   std::memset(out, 0, sizeof(*out));
   out->cells = g->hg.ncells;
-  out->tiles = (long long)g->htiles.size();
-  out->tile_rows = g->shape.rows;
-  const bool gen = g->hg.gen3 && !g->htiles.empty();
-  out->tile_cols = gen ? g->htiles[0].ncol : 64;
-  out->tile_ny = gen ? g->htiles[0].ny : (g->hg.ndim == 3 ? g->shape.ny : 1);
-  out->launch_blocks = g->plan.sets.empty() ? 0 : fvexec::launch_grid(g->plan.sets[0], 0);
+  const std::vector<fvk::DevTile>& tiles = g->htiles[g->list];
+  out->tiles = (long long)tiles.size();
+  out->tile_rows = g->shape[g->list].rows;
+  const bool gen = g->hg.gen3 && !tiles.empty();
+  out->tile_cols = gen ? tiles[0].ncol : 64;
+  out->tile_ny = gen ? tiles[0].ny : (g->hg.ndim == 3 ? g->shape[0].ny : 1);
+  out->launch_blocks = g->plan.sets.empty() ? 0 : fvexec::launch_grid(g->plan.sets[0], 0, g->plan.ns);
   out->workspace_bytes = g->L.total;
   for (int s = 0; s < 4; ++s) out->last_stage_ms[s] = g->last_ms[s];
   return FV_OK;
@@ -434,14 +449,15 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
   if (p->mu > 0.0 && g->hg.ndim != 2)
     return set_error(FV_E_UNSUPPORTED, "the viscous flux is provided for 2D grids only");
   const bool tns = ns_kernel(g->hg, p);
-  g->plan.ns = tns;
+  use_list(g, tns);
+  TileShape& shape = g->shape[g->list];
   {
     // a shape already recorded for this size class and precision is applied
     // as is; the state is untouched, only the per-tile minima are redone
     TileShape rec;
     if (tune_lookup(tune_path(cache_path), tune_key(g->hg, p->precision, tns), rec)) {
-      if (rec.rows != g->shape.rows || rec.ny != g->shape.ny) {
-        g->shape = rec;
+      if (rec.rows != shape.rows || rec.ny != shape.ny) {
+        shape = rec;
         if ((st = upload_tiles(g))) return st;
         if ((st = cfl_pass(g))) return st;
       }
@@ -476,6 +492,11 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
         cands.push_back(s);
       }
   }
+  // and the shape an untuned grid gets, where it is none of these
+  const TileShape def = default_shape(g->hg, tns);
+  if (std::none_of(cands.begin(), cands.end(),
+                   [&](const TileShape& c) { return c.rows == def.rows && c.ny == def.ny; }))
+    cands.push_back(def);
   const int fp32 = p->precision == FV_FP32_FLUX;
   const int rk = fvrt::rk_of(p);
   // the two timing events are released on every return path
@@ -497,12 +518,12 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
   // large grids take batches of at least about 8 ms.
   const int reps = g->hg.ncells < (1LL << 21) ? 64 : 8;
   auto time_shape = [&](const TileShape& c, double& per) -> int {
-    g->shape = c;
+    shape = c;
     int e = upload_tiles(g);
     if (e) return e;
     // same starting state for every candidate (with this candidate's tiles)
     g->hinst = keep;
-    g->hinst.ntiles = (int)g->htiles.size();
+    g->hinst.ntiles = (int)g->htiles[g->list].size();
     params_to_inst(p, g->hg.gamma, g->hinst);
     g->hinst.step_limit = keep.steps + 1000000;
     g->hinst.drop_tol = 0.0;
@@ -548,7 +569,7 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
     st = time_shape(cands[order[r]], again);
     ms[order[r]] = std::min(ms[order[r]], again);
   }
-  TileShape best = g->shape;
+  TileShape best = shape;
   double best_ms = 1e30;
   for (size_t c = 0; c < cands.size(); ++c)
     if (ms[c] < best_ms) {
@@ -556,13 +577,13 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
       best = cands[c];
     }
   if (st) return st;
-  g->shape = best;
+  shape = best;
   st = upload_tiles(g);
   if (st) return st;
   FV_HIP(hipMemcpyAsync(g->d_u[0], saved.data(), sizeof(double) * saved.size(),
                         hipMemcpyHostToDevice, g->stream));
   g->hinst = keep;
-  g->hinst.ntiles = (int)g->htiles.size();
+  g->hinst.ntiles = (int)g->htiles[g->list].size();
   st = put_inst(g, true);
   if (st) return st;
   // the per-tile spectral minima of the restored state

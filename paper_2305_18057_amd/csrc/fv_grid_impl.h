@@ -12,15 +12,18 @@ struct fv_grid {
   size_t ws_bytes = 0;
   fvk::DevBlock* d_blocks = nullptr;
   fvk::DevInstance* d_inst = nullptr;
-  int* d_ntiles = nullptr;
-  fvk::DevTile* d_tiles = nullptr;
+  int* d_ntiles = nullptr;  // counts of the two lists
+  // tile lists of the Euler ([0]) and the Navier-Stokes stage kernel ([1]); the
+  // same one where the grid alone decides the kernel (HostGrid::two_lists)
+  fvk::DevTile* d_tiles[2] = {nullptr, nullptr};
   double* d_part = nullptr;
   fvk::GhostSeg* d_segs = nullptr;
   double* d_u[3] = {nullptr, nullptr, nullptr};
   std::vector<fvk::DevBlock> hblocks;
-  std::vector<fvk::DevTile> htiles;
+  std::vector<fvk::DevTile> htiles[2];
   fvk::DevInstance hinst;
-  fvrt::TileShape shape;
+  fvrt::TileShape shape[2];
+  int list = 0;  // the list in use
   fvexec::StepPlan plan;
   fvexec::GraphCache graphs;
   int have_state = 0;
@@ -39,6 +42,8 @@ int upload_tiles(fv_grid* g);
 int put_inst(fv_grid* g, bool whole);
 int get_inst(fv_grid* g);
 int cfl_pass(fv_grid* g);
+// parameters of a call to the device, with the tile list and the stage kernel
+// they take
 int use_params(fv_grid* g, const fv_params* p);
 
 }  // namespace fvgrid

@@ -49,8 +49,8 @@ int scratch_of_device(char** out) {
 // Scratch layout: the grid layout of an instance without its U^n buffer (the
 // caller's state takes that role), i.e. descriptors, tiles, partials, ghost
 // segments, nodes, then the two stage buffers.
-InstLayout noalloc_layout(const HostGrid& hg) {
-  InstLayout L = layout_of(hg, true);
+InstLayout noalloc_layout(const HostGrid& hg, long long tiles) {
+  InstLayout L = layout_of(hg, tiles);
   const size_t sbytes = align_up(sizeof(double) * (size_t)hg.state_size);
   L.u[1] = L.u[0];
   L.u[2] = L.u[0] + sbytes;
@@ -77,7 +77,7 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
   if (p->mu > 0.0 && hg.ndim != 2)
     return set_error(FV_E_UNSUPPORTED, "the viscous flux is provided for 2D grids only");
   const bool ns = p->mu > 0.0 || hg.has_noslip;
-  const InstLayout L = noalloc_layout(hg);
+  InstLayout L = noalloc_layout(hg, scratch_tiles_of(hg));
   if (L.total > kScratchBytes)
     return set_error(FV_E_NOMEM,
                      "grid needs %zu bytes of static scratch (descriptors, tiles, partials, nodes, "
@@ -92,6 +92,28 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
   if (st) return st;
   hipStream_t s = (hipStream_t)hip_stream;
 
+  TileShape sh = default_shape(hg, ns);
+  {
+    TileShape tsh;
+    if (tune_lookup(tune_path(nullptr), tune_key(hg, p->precision, ns), tsh)) sh = tsh;
+  }
+  std::vector<fvk::DevTile> htiles;
+  build_tiles(hg, sh, 0, 0, htiles);
+  // the list of low tiles can be longer than reserved above: taller ones where
+  // the scratch has no room for it
+  while ((long long)htiles.size() > L.max_tiles) {
+    const InstLayout M = noalloc_layout(hg, (long long)htiles.size());
+    if (M.total <= kScratchBytes) {
+      L = M;
+      break;
+    }
+    if (sh.rows >= 64) break;
+    sh.rows *= 2;
+    build_tiles(hg, sh, 0, 0, htiles);
+  }
+  const int nt = (int)htiles.size();
+  if (nt > L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");
+
   // descriptors: the stage buffers in scratch, U^n the caller's array
   std::vector<fvk::DevBlock> hblocks;
   build_blocks(hg, base, L, 0, hblocks, 0);
@@ -102,21 +124,6 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
       soff += B.ncell * hg.nv;
     }
   }
-  TileShape sh = default_shape(hg);
-  {
-    TileShape tsh;
-    if (tune_lookup(tune_path(nullptr), tune_key(hg, p->precision, ns), tsh)) sh = tsh;
-  }
-  std::vector<fvk::DevTile> htiles;
-  build_tiles(hg, sh, 0, 0, htiles);
-  // a general 3D grid of a few rows can need more tiles of few planes than
-  // the scratch holds: fewer, taller ones
-  while ((long long)htiles.size() > L.max_tiles && sh.rows < 64) {
-    sh.rows *= 2;
-    build_tiles(hg, sh, 0, 0, htiles);
-  }
-  const int nt = (int)htiles.size();
-  if (nt > L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");
 
   fvk::DevBlock* d_blocks = (fvk::DevBlock*)(base + L.blocks);
   fvk::DevInstance* d_inst = (fvk::DevInstance*)(base + L.inst);

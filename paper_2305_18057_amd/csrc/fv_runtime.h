@@ -49,21 +49,27 @@ struct HostGrid {
   int nphantom = 0;
   long long phantom_cells = 0;
   long long compute_cells() const { return ncells - phantom_cells; }
+  // whether the stage kernel of a 2D grid depends on the parameters of a call
+  // (a viscosity without a no-slip face or a source): it keeps a tile list for
+  // the Euler and one for the Navier-Stokes kernel
+  bool two_lists() const { return ndim == 2 && !has_noslip && !with_source; }
 };
 
 int validate_and_copy(const fv_grid_desc* d, HostGrid& out);
 
 // size of the per-instance device region and its layout
 struct InstLayout {
-  size_t blocks, inst, ntiles, tiles, part, segs, nodes, src, u[3], total;
+  size_t blocks, inst, ntiles, tiles, tiles_ns, part, segs, nodes, src, u[3], total;
   long long max_tiles;
   int nseg;
   long long ghost_cells, ghost_doubles;
 };
-long long max_tiles_of(const HostGrid& g);
-// fixed_scratch: the tile list of the allocation-free path, which makes its
-// tiles taller where a list would not fit
-InstLayout layout_of(const HostGrid& g, bool fixed_scratch = false);
+// tiles >= 0: room for one list of that many (the allocation-free path, whose
+// kernel is known); -1: for every shape and kernel a grid handle may take
+InstLayout layout_of(const HostGrid& g, long long tiles = -1);
+// the tiles by which the allocation-free path decides whether a grid fits its
+// scratch (2 rows, 4 planes; a list that is longer gets taller tiles)
+long long scratch_tiles_of(const HostGrid& g);
 
 // fill host mirrors (blocks, ghost segments) for an instance placed at `base`
 void build_blocks(const HostGrid& g, char* base, const InstLayout& L, int inst_index,
@@ -74,7 +80,8 @@ void build_segs(const HostGrid& g, std::vector<fvk::GhostSeg>& segs);
 hipError_t upload_nodes(const HostGrid& g, char* dst, hipStream_t s);
 void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int block_index_offset,
                  std::vector<fvk::DevTile>& out);
-TileShape default_shape(const HostGrid& g);
+// ns: for the Navier-Stokes stage kernel; shared: beside other instances of a server
+TileShape default_shape(const HostGrid& g, bool ns, bool shared = false);
 // columns and rows of the general 3D kernel's tiles of an ni x nj block
 void gen_tile_shape(int ni, int nj, int& w, int& h);
 int size_class(const HostGrid& g);

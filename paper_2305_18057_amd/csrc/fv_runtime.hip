@@ -155,7 +155,7 @@ int validate_and_copy(const fv_grid_desc* d, HostGrid& g) {
   }
 }
 
-static const int kMinRows2D = 2, kMinPlanes3D = 4, kMinNy3D = 3;
+static const int kMinRows2D = 1, kMinPlanes3D = 1, kMinNy3D = 3;
 
 // Every split of the columns into even parts, with the most rows for which
 // one thread each is enough for the (W + 1) H i-faces, the W (H + 1) j-faces
@@ -183,12 +183,13 @@ void gen_tile_shape(int ni, int nj, int& w, int& h) {
   }
 }
 
-long long max_tiles_of(const HostGrid& g) {
+// rows, planes: the least rows of a 2D tile, planes of a 3D one
+static long long max_tiles_of(const HostGrid& g, int rows, int planes) {
   long long t = 0;
   for (const auto& B : g.blocks) {
     const long long ci = (B.ni + 63) / 64;
-    if (g.ndim == 2) t += ci * ((B.nj + kMinRows2D - 1) / kMinRows2D);
-    else t += ci * ((B.nj + kMinNy3D - 1) / kMinNy3D) * ((B.nk + kMinPlanes3D - 1) / kMinPlanes3D);
+    if (g.ndim == 2) t += ci * ((B.nj + rows - 1) / rows);
+    else t += ci * ((B.nj + kMinNy3D - 1) / kMinNy3D) * ((B.nk + planes - 1) / planes);
   }
   return t;
 }
@@ -222,10 +223,15 @@ void build_segs(const HostGrid& g, std::vector<fvk::GhostSeg>& segs) {
     }
 }
 
-InstLayout layout_of(const HostGrid& g, bool fixed_scratch) {
+long long scratch_tiles_of(const HostGrid& g) { return max_tiles_of(g, 2, 4); }
+
+InstLayout layout_of(const HostGrid& g, long long tiles) {
   InstLayout L;
-  L.max_tiles = max_tiles_of(g);
-  if (g.gen3 && !fixed_scratch) L.max_tiles = std::max(L.max_tiles, max_gen_tiles(g));
+  L.max_tiles = tiles;
+  if (tiles < 0) {
+    L.max_tiles = max_tiles_of(g, kMinRows2D, kMinPlanes3D);
+    if (g.gen3) L.max_tiles = std::max(L.max_tiles, max_gen_tiles(g));
+  }
   std::vector<fvk::GhostSeg> segs;
   build_segs(g, segs);
   L.nseg = (int)segs.size();
@@ -237,6 +243,11 @@ InstLayout layout_of(const HostGrid& g, bool fixed_scratch) {
   L.inst = off;   off += align_up(sizeof(fvk::DevInstance));
   L.ntiles = off; off += align_up(sizeof(int) * 4);
   L.tiles = off;  off += align_up(sizeof(fvk::DevTile) * (size_t)L.max_tiles);
+  L.tiles_ns = L.tiles;
+  if (g.two_lists() && tiles < 0) {
+    L.tiles_ns = off;
+    off += align_up(sizeof(fvk::DevTile) * (size_t)L.max_tiles);
+  }
   L.part = off;   off += align_up(sizeof(double) * fvk::kPartStride * (size_t)L.max_tiles);
   L.segs = off;   off += align_up(sizeof(fvk::GhostSeg) * (size_t)L.nseg);
   L.nodes = off;  off += align_up(sizeof(double) * (size_t)g.node_doubles);
@@ -323,22 +334,98 @@ hipError_t upload_nodes(const HostGrid& g, char* dst, hipStream_t s) {
   return hipSuccess;
 }
 
-TileShape default_shape(const HostGrid& g) {
+// Time of a stage launch by a model of its rounds, in microseconds: an XCD's
+// part of the tile list (an eighth, see xcd_walk) runs in rounds of as many
+// tiles as it holds at once, each c + b n for tiles of n rows or planes; a
+// last round that fills at most half of that leaves its tiles a SIMD of their
+// own and takes c1 + b1 n.  f is paid once.  The coefficients are fitted to
+// timed sweeps of n on an MI355X (FP64; FP32-flux has the same best shapes):
+// 2D inlets of 8 k to 4.2 M cells, 3D boxes of 32^3 to 256^3.
+struct RoundModel {
+  int per_cu;  // tiles a CU holds at once
+  double f, c, b, c1, b1;
+};
+static const RoundModel kRounds2D = {8, 7.0, 3.0, 3.3, 1.0, 1.95};
+static const RoundModel kRounds3D7 = {1, 0.0, 9.0, 3.4, 9.0, 3.4};
+static const RoundModel kRounds3D3 = {2, 0.0, 5.6, 3.3, 5.6, 2.1};
+static const RoundModel kRounds3DG = {2, 0.0, 6.0, 7.4, 6.0, 4.7};
+
+static double model_us(const RoundModel& M, long long tiles, int n) {
+  const long long part = (tiles + fvk::kXcds - 1) / fvk::kXcds;
+  const long long slots = std::max(1, M.per_cu * device_cu_count() / fvk::kXcds);
+  const long long full = part / slots, rest = part % slots;
+  double t = M.f + full * (M.c + M.b * n);
+  if (rest > 0) t += 2 * rest <= slots ? M.c1 + M.b1 * n : M.c + M.b * n;
+  return t;
+}
+
+// The shape a grid gets without a tuned one.  A served instance (shared) runs
+// beside others that fill the device, so it keeps tall tiles (the least work
+// per cell); a grid of its own gets the shape whose rounds the model finds
+// shortest.  Of the even splits of the rows (planes), at most 64 of them per
+// tile: with the fixed 4 rows or 32 x 7 planes before, a 99 x 90 x 77 box ran
+// on 78 of 256 CUs (255 us a step, now 125) and a 128 x 64 grid in
+// 32 tiles (43 us, now 33); 256^3 in five rounds where three taller ones do.
+TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
   TileShape s;
-  if (g.ndim == 2) {
-    // aim for about 8 wavefronts per SIMD across the chip, 4..64 rows
-    const long long cells = g.ncells;
-    long long want = cells / (64LL * 8192);
-    int rows = 4;
-    while (rows < 64 && rows * 2 <= want) rows *= 2;
-    s.rows = rows;
+  if (shared) {
+    if (g.ndim == 2) {
+      // aim for about 8 wavefronts per SIMD across the chip, 4..64 rows
+      const long long want = g.ncells / (64LL * 8192);
+      s.rows = 4;
+      while (s.rows < 64 && s.rows * 2 <= want) s.rows *= 2;
+      s.ny = 1;
+    } else {
+      s.ny = g.gen3 ? 4 : 7;
+      s.rows = g.gen3 ? 16 : 32;
+    }
+    return s;
+  }
+  // tiles of n rows (planes), h j-rows each in 3D
+  auto tiles_of = [&](int n, int ny) {
+    long long t = 0;
+    for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
+      const fv_block_desc& B = g.blocks[b];
+      int w = 64, h = ny;
+      if (g.gen3) gen_tile_shape(B.ni, B.nj, w, h);
+      const long long ci = (B.ni + w - 1) / w;
+      t += g.ndim == 2 ? ci * ((B.nj + n - 1) / n)
+                       : ci * ((B.nj + h - 1) / h) * ((B.nk + n - 1) / n);
+    }
+    return t;
+  };
+  if (g.ndim == 2 && ns) {
+    // slabs of 4 rows, and twice as many while eight tiles per CU are left: the
+    // three workgroups of a CU drift apart and fill each other's waits, so
+    // even rounds matter less than a short tail (524 k cells: 117, 123, 123 and
+    // 134 us a step with 4, 8, 12 and 16 rows; 1.05 M: 214, 204, 211, 218)
+    s.rows = 4;
     s.ny = 1;
-  } else if (g.gen3) {
-    s.ny = 4;
-    s.rows = 16;
-  } else {
-    s.ny = 7;
-    s.rows = 32;
+    while (s.rows < 64 && tiles_of(2 * s.rows, 1) >= 8LL * device_cu_count()) s.rows *= 2;
+    return s;
+  }
+  int nmax = 1;
+  for (int b = 0; b < g.nblocks - g.nphantom; ++b)
+    nmax = std::max(nmax, g.ndim == 2 ? g.blocks[b].nj : g.blocks[b].nk);
+  const RoundModel* M = g.ndim == 2 ? &kRounds2D : (g.gen3 ? &kRounds3DG : &kRounds3D7);
+  double best = -1.0;
+  for (int ny : {7, 3}) {
+    if (ny == 3) {
+      if (g.ndim == 2 || g.gen3) break;
+      M = &kRounds3D3;
+    }
+    for (int parts = (nmax + 63) / 64; parts <= nmax; ++parts) {
+      const int n = (nmax + parts - 1) / parts;
+      const double t = model_us(*M, tiles_of(n, ny), n);
+      if (best < 0.0 || t < best) {
+        best = t;
+        s.rows = n;
+        s.ny = g.ndim == 2 ? 1 : (g.gen3 ? 4 : ny);
+      }
+      // the next count of parts that gives lower tiles
+      if (n <= 1) break;
+      parts = std::max(parts, (nmax + n - 2) / (n - 1) - 1);
+    }
   }
   return s;
 }

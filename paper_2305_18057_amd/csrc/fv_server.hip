@@ -571,7 +571,7 @@ int submit(fv_server* S, const fv_grid_desc* desc, const double* U0, const doubl
   r->params.precision = S->d.precision;
   r->drop_tol = drop_tol;
   r->max_steps = max_steps;
-  TileShape sh = default_shape(r->hg);
+  TileShape sh = default_shape(r->hg, ns, true);
   TileShape tsh;
   if (tune_lookup(tune_path(S->tune_path.empty() ? nullptr : S->tune_path.c_str()),
                   tune_key(r->hg, S->d.precision, ns), tsh))
