@@ -55,17 +55,22 @@ int upload_tiles(fv_grid* g) {
   return FV_OK;
 }
 
-int put_inst(fv_grid* g, bool whole) {
-  const size_t n = whole ? sizeof(fvk::DevInstance) : offsetof(fvk::DevInstance, t);
-  FV_HIP(hipMemcpyAsync(g->d_inst, &g->hinst, n, hipMemcpyHostToDevice, g->stream));
+// the whole record to the device
+int put_inst(fv_grid* g) {
+  FV_HIP(fvk::launch_put(g->stream, g->d_inst, g->hinst, true, false));
+  return FV_OK;
+}
+
+// the record the kernels have left in pinned memory, once they are done
+static int wait_inst(fv_grid* g) {
+  FV_HIP(hipStreamSynchronize(g->stream));
+  g->hinst = *g->pin;
   return FV_OK;
 }
 
 int get_inst(fv_grid* g) {
-  FV_HIP(hipMemcpyAsync(&g->hinst, g->d_inst, sizeof(fvk::DevInstance), hipMemcpyDeviceToHost,
-                        g->stream));
-  FV_HIP(hipStreamSynchronize(g->stream));
-  return FV_OK;
+  FV_HIP(fvk::launch_publish(g->stream, g->d_inst, g->pin));
+  return wait_inst(g);
 }
 
 void fill_info(const fv_grid* g, fv_step_info* info) {
@@ -83,10 +88,10 @@ void fill_info(const fv_grid* g, fv_step_info* info) {
 int cfl_pass(fv_grid* g) {
   const int err = fvexec::enqueue_cfl(g->plan, g->stream);
   if (err) return err;
-  FV_HIP(fvk::launch_cfl_init(g->stream, g->d_inst, nullptr, 1));
+  FV_HIP(fvk::launch_cfl_init(g->stream, g->d_inst, nullptr, 1, g->pin));
   g->cfl_mu = g->hinst.mu;
   g->cfl_pr = g->hinst.prandtl;
-  return get_inst(g);
+  return wait_inst(g);
 }
 
 // 2D grids run the Navier-Stokes stage kernel for a viscosity, a no-slip
@@ -99,15 +104,16 @@ bool ns_kernel(const HostGrid& hg, const fv_params* p) {
 // needs the Navier-Stokes kernel (2D grids).  hinst holds the parameters; when
 // the viscosity differs from the one the current time-step bound was formed
 // with, the bound is formed again.
-int use_params(fv_grid* g, const fv_params* p) {
-  use_list(g, ns_kernel(g->hg, p));
-  int st = put_inst(g, false);
-  if (st) return st;
+int use_params(fv_grid* g, const fv_params* p, bool prepare) {
   if (p->mu > 0.0 && g->hg.ndim != 2)
     return set_error(FV_E_UNSUPPORTED, "the viscous flux is provided for 2D grids only");
-  if (g->have_state && (g->hinst.mu != g->cfl_mu || g->hinst.prandtl != g->cfl_pr)) {
-    st = cfl_pass(g);
+  use_list(g, ns_kernel(g->hg, p));
+  const bool redo = g->have_state && (g->hinst.mu != g->cfl_mu || g->hinst.prandtl != g->cfl_pr);
+  FV_HIP(fvk::launch_put(g->stream, g->d_inst, g->hinst, false, prepare && !redo));
+  if (redo) {
+    const int st = cfl_pass(g);
     if (st) return st;
+    if (prepare) FV_HIP(fvk::launch_prepare(g->stream, g->d_inst, nullptr, 1));
   }
   return FV_OK;
 }
@@ -168,6 +174,10 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
     delete g;
     return e;
   };
+  if (hipHostMalloc((void**)&g->pin, sizeof(fvk::DevInstance), hipHostMallocDefault) != hipSuccess) {
+    g->pin = nullptr;
+    return fail(set_error(FV_E_NOMEM, "pinned host allocation failed"));
+  }
   hipError_t he = hipMemcpyAsync(g->d_blocks, g->hblocks.data(),
                                  sizeof(fvk::DevBlock) * g->hblocks.size(), hipMemcpyHostToDevice,
                                  g->stream);
@@ -208,7 +218,7 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
   g->plan.ns = g->hg.ndim == 2 && !g->hg.two_lists();
   st = fvgrid::upload_tiles(g);
   if (st) return fail(st);
-  st = fvgrid::put_inst(g, true);
+  st = fvgrid::put_inst(g);
   if (st) return fail(st);
   he = hipStreamSynchronize(g->stream);
   if (he != hipSuccess)
@@ -237,7 +247,7 @@ extern "C" int fv_set_state(fv_grid* g, const double* U, int on_device) {
   I.stopped = 0;
   I.have_first = 0;
   I.last_step = 0;
-  int st = put_inst(g, true);
+  int st = put_inst(g);
   if (st) return st;
   st = cfl_pass(g);
   if (st) return st;
@@ -277,16 +287,16 @@ extern "C" int fv_residual(fv_grid* g, const fv_params* p, double* R, int on_dev
   if (st) return st;
   if (!g->have_state) return set_error(FV_E_INVAL, "no state set");
   params_to_inst(p, g->hg.gamma, g->hinst);
-  if ((st = use_params(g, p))) return st;
+  if ((st = use_params(g, p, false))) return st;
   double* dst = (R && on_device) ? R : g->d_u[1];
   g->plan.lim = p->limiter;
   st = fvexec::enqueue_stage(g->plan, 0, p->precision == FV_FP32_FLUX, dst, g->stream);
   if (st) return st;
-  FV_HIP(fvk::launch_rnorms(g->stream, g->d_inst, nullptr, 1));
+  FV_HIP(fvk::launch_rnorms(g->stream, g->d_inst, nullptr, 1, g->pin));
   if (R && !on_device)
     FV_HIP(hipMemcpyAsync(R, g->d_u[1], sizeof(double) * g->hg.state_size, hipMemcpyDeviceToHost,
                           g->stream));
-  st = get_inst(g);
+  st = wait_inst(g);
   if (st) return st;
   if (norms)
     for (int v = 0; v < 5; ++v) norms[v] = g->hinst.rnorms[v];
@@ -323,8 +333,7 @@ static int run_steps(fv_grid* g, const fv_params* p, long long nsteps, double dr
   params_to_inst(p, g->hg.gamma, g->hinst);
   g->hinst.drop_tol = drop_tol;
   g->hinst.step_limit = g->hinst.steps + nsteps;
-  if ((st = use_params(g, p))) return st;
-  FV_HIP(fvk::launch_prepare(g->stream, g->d_inst, nullptr, 1));
+  if ((st = use_params(g, p, true))) return st;
   const int fp32 = p->precision == FV_FP32_FLUX;
   g->plan.rk = fvrt::rk_of(p);
   g->plan.lim = p->limiter;
@@ -370,8 +379,7 @@ extern "C" int fv_step_timed(fv_grid* g, const fv_params* p, int nsteps, fv_step
   params_to_inst(p, g->hg.gamma, g->hinst);
   g->hinst.drop_tol = 0.0;
   g->hinst.step_limit = g->hinst.steps + nsteps;
-  if ((st = use_params(g, p))) return st;
-  FV_HIP(fvk::launch_prepare(g->stream, g->d_inst, nullptr, 1));
+  if ((st = use_params(g, p, true))) return st;
   const int fp32 = p->precision == FV_FP32_FLUX;
   // the events are released on every return path
   struct Events {
@@ -531,7 +539,7 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
     g->hinst.flags = 0;
     g->plan.rk = rk;
     g->plan.lim = p->limiter;
-    if ((e = put_inst(g, true))) return e;
+    if ((e = put_inst(g))) return e;
     if ((e = fvexec::enqueue_steps(g->plan, fp32, reps, g->stream, &g->graphs))) return e;
     per = 1e30;
     for (int b = 0; b < 3 && !e; ++b) {
@@ -584,7 +592,7 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
                         hipMemcpyHostToDevice, g->stream));
   g->hinst = keep;
   g->hinst.ntiles = (int)g->htiles[g->list].size();
-  st = put_inst(g, true);
+  st = put_inst(g);
   if (st) return st;
   // the per-tile spectral minima of the restored state
   st = cfl_pass(g);

@@ -22,6 +22,7 @@ struct fv_grid {
   std::vector<fvk::DevBlock> hblocks;
   std::vector<fvk::DevTile> htiles[2];
   fvk::DevInstance hinst;
+  fvk::DevInstance* pin = nullptr;  // pinned: where the kernels leave the record of a call
   fvrt::TileShape shape[2];
   int list = 0;  // the list in use
   fvexec::StepPlan plan;
@@ -31,6 +32,9 @@ struct fv_grid {
   // viscosity with which the device's time-step bound of the current state
   // was formed (the viscous term enters it)
   double cfl_mu = 0.0, cfl_pr = 0.0;
+  ~fv_grid() {
+    if (pin) (void)hipHostFree(pin);
+  }
 };
 
 namespace fvgrid {
@@ -39,11 +43,11 @@ namespace fvgrid {
 // split's GPU part, whose halo block is read but never computed)
 int create(fvrt::HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_stream, fv_grid** out);
 int upload_tiles(fv_grid* g);
-int put_inst(fv_grid* g, bool whole);
+int put_inst(fv_grid* g);
 int get_inst(fv_grid* g);
 int cfl_pass(fv_grid* g);
 // parameters of a call to the device, with the tile list and the stage kernel
-// they take
-int use_params(fv_grid* g, const fv_params* p);
+// they take; prepare: the stop flags and the time step of the coming steps too
+int use_params(fv_grid* g, const fv_params* p, bool prepare);
 
 }  // namespace fvgrid

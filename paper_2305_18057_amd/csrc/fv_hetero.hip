@@ -837,8 +837,7 @@ extern "C" int fv_hetero_step(fv_hetero* h, const fv_params* p, int nsteps, fv_s
   g->hinst.t_end = 0.0;
   g->hinst.drop_tol = 0.0;
   g->hinst.step_limit = LLONG_MAX;
-  if ((st = fvgrid::use_params(g, p))) return st;
-  FV_HIP(fvk::launch_prepare(g->stream, g->d_inst, nullptr, 1));
+  if ((st = fvgrid::use_params(g, p, true))) return st;
   g->plan.rk = rk;
   g->plan.lim = p->limiter;
   const int fp32 = p->precision == FV_FP32_FLUX;

@@ -47,11 +47,19 @@ const void* stage3d_gen_kernel_ptr(int fp32);
 //             flags, stop rule, next time step
 //   cfl_init: spectral minimum and physical check after a new state
 //   rnorms:   norms of a residual-only evaluation
+//   put:      a record's parameters (whole: all of it) to the device as a kernel
+//             argument, and with prep the work of prepare
+//   publish:  a record to pinned host memory (as cfl_init and rnorms do with a
+//             host address); complete when the stream is
 hipError_t launch_prepare(hipStream_t s, DevInstance* insts, const int* active, int n);
 hipError_t launch_finalize(hipStream_t s, DevInstance* insts, const int* active, int n,
                            const int* n_dev = nullptr);
-hipError_t launch_cfl_init(hipStream_t s, DevInstance* insts, const int* active, int n);
-hipError_t launch_rnorms(hipStream_t s, DevInstance* insts, const int* active, int n);
+hipError_t launch_cfl_init(hipStream_t s, DevInstance* insts, const int* active, int n,
+                           DevInstance* host = nullptr);
+hipError_t launch_rnorms(hipStream_t s, DevInstance* insts, const int* active, int n,
+                         DevInstance* host = nullptr);
+hipError_t launch_put(hipStream_t s, DevInstance* inst, const DevInstance& v, bool whole, bool prep);
+hipError_t launch_publish(hipStream_t s, const DevInstance* inst, DevInstance* host);
 
 // ghost values of the current state in the documented dump layout
 struct GhostSeg {

@@ -1,6 +1,8 @@
 // Per-instance bookkeeping kernels: parameters -> time step and stop flags,
 // step-end reductions of the per-tile partials (fixed order: lane l sums
 // tiles l, l+64, ... then a fixed butterfly), and the ghost dump.
+#include <cstddef>
+
 #include "fv_device.h"
 #include "fv_launch.h"
 
@@ -27,10 +29,8 @@ __device__ __forceinline__ void next_dt(DevInstance& I) {
   I.last_step = last;
 }
 
-__global__ void k_prepare(DevInstance* insts, const int* active, int n) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  if (x >= n) return;
-  DevInstance& I = insts[active ? active[x] : x];
+// stop flags and time step of the coming steps from the parameters
+__device__ __forceinline__ void prepare(DevInstance& I) {
   I.flags &= FLAG_NONPHYS;
   I.stopped = (I.flags & FLAG_NONPHYS) ? 1 : 0;
   if (I.steps >= I.step_limit) {
@@ -38,6 +38,37 @@ __global__ void k_prepare(DevInstance* insts, const int* active, int n) {
     I.flags |= FLAG_STEPLIMIT;
   }
   if (!I.stopped) next_dt(I);
+}
+
+__global__ void k_prepare(DevInstance* insts, const int* active, int n) {
+  const int x = blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= n) return;
+  prepare(insts[active ? active[x] : x]);
+}
+
+// An instance record moves as words, one per lane: from a kernel argument to
+// the device (the launch carries it: no copy from the caller's pageable memory
+// on the stream), and from the device to pinned host memory at the end of a
+// call.  A put, two empty kernels, a publish and the wait for them take 18 us;
+// with a copy in each direction in their place 29 us.
+constexpr int kInstWords = sizeof(DevInstance) / 8;
+static_assert(sizeof(DevInstance) % 8 == 0 && kInstWords <= 64, "one word per lane");
+struct InstWords {
+  unsigned long long w[kInstWords];
+};
+__device__ __forceinline__ void publish(const DevInstance* inst, DevInstance* host) {
+  const int x = threadIdx.x;
+  if (x < kInstWords)
+    ((unsigned long long*)host)[x] = ((const unsigned long long*)inst)[x];
+}
+__global__ __launch_bounds__(64) void k_put(DevInstance* inst, InstWords v, int words, int prep) {
+  const int x = threadIdx.x;
+  if (x < words) ((unsigned long long*)inst)[x] = v.w[x];
+  __syncthreads();
+  if (prep && x == 0) prepare(*inst);
+}
+__global__ __launch_bounds__(64) void k_publish(const DevInstance* inst, DevInstance* host) {
+  publish(inst, host);
 }
 
 // Sums of the per-tile partials of one instance by a workgroup of kRedThreads
@@ -200,19 +231,23 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize(DevInstance* insts, co
   I.last_step = last_step;
 }
 
+// host: the record goes there too (one instance), or null
 __global__ __launch_bounds__(kRedThreads) void k_cfl_init(DevInstance* insts, const int* active,
-                                                         int n) {
+                                                         int n, DevInstance* host) {
   DevInstance& I = insts[active ? active[blockIdx.x] : blockIdx.x];
   RedOut R;
   reduce_parts(I.ntiles, I.part, false, true, R);
-  if (threadIdx.x != 0) return;
-  I.raw_min = R.mn;
-  I.flags = R.bad ? FLAG_NONPHYS : 0;
-  I.stopped = R.bad ? 1 : 0;
+  if (threadIdx.x == 0) {
+    I.raw_min = R.mn;
+    I.flags = R.bad ? FLAG_NONPHYS : 0;
+    I.stopped = R.bad ? 1 : 0;
+  }
+  __syncthreads();
+  if (host) publish(&I, host);
 }
 
 __global__ __launch_bounds__(kRedThreads) void k_rnorms(DevInstance* insts, const int* active,
-                                                       int n) {
+                                                       int n, DevInstance* host) {
   DevInstance& I = insts[active ? active[blockIdx.x] : blockIdx.x];
   const int nv = I.nv;
   const long long ncells = I.ncells;
@@ -221,11 +256,14 @@ __global__ __launch_bounds__(kRedThreads) void k_rnorms(DevInstance* insts, cons
   for (int v = 0; v < 5; ++v) qref[v] = I.qref[v];
   RedOut R;
   reduce_parts(I.ntiles, I.part, true, false, R);
-  if (threadIdx.x != 0) return;
-  double comb, rn[5];
-  norms_from_sums(nv, ncells, qref, R.s, rn, comb);
+  if (threadIdx.x == 0) {
+    double comb, rn[5];
+    norms_from_sums(nv, ncells, qref, R.s, rn, comb);
 #pragma unroll
-  for (int v = 0; v < 5; ++v) I.rnorms[v] = rn[v];
+    for (int v = 0; v < 5; ++v) I.rnorms[v] = rn[v];
+  }
+  __syncthreads();
+  if (host) publish(&I, host);
 }
 
 // One thread per ghost cell.  Segment = (block, face): both layers.
@@ -269,14 +307,27 @@ hipError_t launch_finalize(hipStream_t s, DevInstance* insts, const int* active,
   hipLaunchKernelGGL(k_finalize, dim3(n), dim3(kRedThreads), 0, s, insts, active, n, n_dev);
   return hipGetLastError();
 }
-hipError_t launch_cfl_init(hipStream_t s, DevInstance* insts, const int* active, int n) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_cfl_init, dim3(n), dim3(kRedThreads), 0, s, insts, active, n);
+hipError_t launch_put(hipStream_t s, DevInstance* inst, const DevInstance& v, bool whole, bool prep) {
+  InstWords w;
+  __builtin_memcpy(&w, &v, sizeof(w));
+  const int words = whole ? kInstWords : (int)(offsetof(DevInstance, t) / 8);
+  hipLaunchKernelGGL(k_put, dim3(1), dim3(64), 0, s, inst, w, words, prep ? 1 : 0);
   return hipGetLastError();
 }
-hipError_t launch_rnorms(hipStream_t s, DevInstance* insts, const int* active, int n) {
+hipError_t launch_publish(hipStream_t s, const DevInstance* inst, DevInstance* host) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, inst, host);
+  return hipGetLastError();
+}
+hipError_t launch_cfl_init(hipStream_t s, DevInstance* insts, const int* active, int n,
+                           DevInstance* host) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rnorms, dim3(n), dim3(kRedThreads), 0, s, insts, active, n);
+  hipLaunchKernelGGL(k_cfl_init, dim3(n), dim3(kRedThreads), 0, s, insts, active, n, host);
+  return hipGetLastError();
+}
+hipError_t launch_rnorms(hipStream_t s, DevInstance* insts, const int* active, int n,
+                         DevInstance* host) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_rnorms, dim3(n), dim3(kRedThreads), 0, s, insts, active, n, host);
   return hipGetLastError();
 }
 hipError_t launch_ghosts(hipStream_t s, const DevBlock* blocks, const GhostSeg* segs, int nseg,

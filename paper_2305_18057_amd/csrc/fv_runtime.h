@@ -76,7 +76,9 @@ void build_blocks(const HostGrid& g, char* base, const InstLayout& L, int inst_i
                   std::vector<fvk::DevBlock>& out, int block_index_offset);
 void build_segs(const HostGrid& g, std::vector<fvk::GhostSeg>& segs);
 // node coordinates of every curvilinear block to dst (the layout's node
-// region): per block x, y (and z in 3D), in block order
+// region): per block x, y (and z in 3D), in block order; pack_nodes: to host
+// memory
+void pack_nodes(const HostGrid& g, char* dst);
 hipError_t upload_nodes(const HostGrid& g, char* dst, hipStream_t s);
 void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int block_index_offset,
                  std::vector<fvk::DevTile>& out);

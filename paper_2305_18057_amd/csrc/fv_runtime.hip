@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <limits>
 #include <mutex>
 #include <sstream>
 
@@ -31,6 +32,13 @@ static void trans(const fv_block_desc& b, int d, int& n1, int& n2) {
   if (d == 0) { n1 = b.nj; n2 = b.nk; }
   else if (d == 1) { n1 = b.ni; n2 = b.nk; }
   else { n1 = b.ni; n2 = b.nj; }
+}
+
+// (no early exit: the loop vectorises)
+static bool all_finite(const std::vector<double>& v) {
+  bool ok = true;
+  for (const double x : v) ok &= std::fabs(x) <= std::numeric_limits<double>::max();
+  return ok;
 }
 
 static int validate_and_copy_impl(const fv_grid_desc* d, HostGrid& g) {
@@ -79,10 +87,8 @@ static int validate_and_copy_impl(const fv_grid_desc* d, HostGrid& g) {
       g.xs[b].assign(B.x, B.x + nn);
       g.ys[b].assign(B.y, B.y + nn);
       if (g.ndim == 3) g.zs[b].assign(B.z, B.z + nn);
-      for (size_t q = 0; q < nn; ++q)
-        if (!std::isfinite(g.xs[b][q]) || !std::isfinite(g.ys[b][q]) ||
-            (g.ndim == 3 && !std::isfinite(g.zs[b][q])))
-          return set_error(FV_E_INVAL, "block %d: non-finite node coordinate", b);
+      if (!all_finite(g.xs[b]) || !all_finite(g.ys[b]) || (g.ndim == 3 && !all_finite(g.zs[b])))
+        return set_error(FV_E_INVAL, "block %d: non-finite node coordinate", b);
       B.x = g.xs[b].data();
       B.y = g.ys[b].data();
       B.z = g.ndim == 3 ? g.zs[b].data() : nullptr;
@@ -316,6 +322,18 @@ void build_blocks(const HostGrid& g, char* base, const InstLayout& L, int inst_i
     }
     out.push_back(B);
     soff += B.ncell * g.nv;
+  }
+}
+
+void pack_nodes(const HostGrid& g, char* dst) {
+  for (int b = 0; b < g.nblocks; ++b) {
+    const std::vector<double>* c[3] = {&g.xs[b], &g.ys[b], &g.zs[b]};
+    for (int a = 0; a < (g.ndim == 3 ? 3 : 2); ++a) {
+      if (c[a]->empty()) continue;
+      const size_t bytes = c[a]->size() * sizeof(double);
+      std::memcpy(dst, c[a]->data(), bytes);
+      dst += bytes;
+    }
   }
 }
 
