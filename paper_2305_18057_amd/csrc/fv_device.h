@@ -67,10 +67,17 @@ struct DevInstance {
 constexpr int kGenThreads = 256;
 constexpr int kGenQ = 456, kGenNd = 272;
 
+// Navier-Stokes kernel: threads per workgroup and the largest slab its arrays
+// hold: staged cells (W + 4)(H + 4), primitives (W + 2)(H + 2), nodes
+// (W + 3)(H + 3) of a slab of W columns and H rows.
+constexpr int kNsThreads = 256;
+constexpr int kNsQ = 448, kNsW = 320, kNsN = 384;
+
 // A tile: 64 consecutive cells along i (ncol of them active), in rows
 // [j0, j0 + ny) (3D) and marching over n rows (2D: along j) or n planes
 // (3D: along k).  The general 3D kernel's tiles are ncol by ny cells of any
-// shape that fits its workgroup.  `local` is the tile's index within its instance.
+// shape that fits its workgroup, the Navier-Stokes kernel's slabs ny rows of
+// ncol cells.  `local` is the tile's index within its instance.
 struct DevTile {
   int blk, inst, local, ncol;
   int i0, j0, k0, n;

@@ -28,7 +28,8 @@ int upload_tiles(fv_grid* g) {
   const int lists = g->hg.two_lists() ? 2 : 1;
   int nt[2] = {0, 0};
   for (int x = 0; x < lists; ++x) {
-    build_tiles(g->hg, g->shape[x], 0, 0, g->htiles[x]);
+    build_tiles(g->hg, g->shape[x], 0, 0, g->htiles[x],
+                g->hg.ndim == 2 && (x == 1 || !g->hg.two_lists()));
     nt[x] = (int)g->htiles[x].size();
     if (nt[x] > g->L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");
     FV_HIP(hipMemcpyAsync(g->d_tiles[x], g->htiles[x].data(), sizeof(fvk::DevTile) * nt[x],
@@ -438,7 +439,7 @@ extern "C" int fv_grid_get_stats(const fv_grid* g, fv_grid_stats* out) {
   out->tiles = (long long)tiles.size();
   out->tile_rows = g->shape[g->list].rows;
   const bool gen = g->hg.gen3 && !tiles.empty();
-  out->tile_cols = gen ? tiles[0].ncol : 64;
+  out->tile_cols = gen || g->plan.ns ? tiles[0].ncol : 64;
   out->tile_ny = gen ? tiles[0].ny : (g->hg.ndim == 3 ? g->shape[0].ny : 1);
   out->launch_blocks = g->plan.sets.empty() ? 0 : fvexec::launch_grid(g->plan.sets[0], 0, g->plan.ns);
   out->workspace_bytes = g->L.total;

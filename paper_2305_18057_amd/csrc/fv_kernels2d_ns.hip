@@ -5,32 +5,35 @@
 // parameters carry a viscosity, whose faces include a no-slip wall or that
 // has a source.
 //
-// One workgroup of 256 threads takes a tile (64 columns by n rows) in slabs
-// of 4 rows, one cell per thread (lane = column, wave = row):
+// One workgroup of 256 threads takes a tile of W columns by n rows in slabs of
+// H rows (the host chooses W and H for the block), one cell per thread:
 //   1. the slab's state with a two-cell halo on every side (corner ghosts
 //      included), u, v and p/rho of the slab and one ring, and the nodes go
-//      to LDS.  Every load of a slab is issued before the first wait: rows are
-//      wave-uniform, so the source of a row (this block, a neighbour, a wall)
-//      is scalar work; the four halo columns of all rows are one wave's third
-//      cell per lane;
+//      to LDS, two cells and two nodes per thread, every load issued before
+//      the first wait;
 //   2. every face of the slab gets its flux once: Roe's flux of the MUSCL
 //      face states (times |S|) minus the viscous flux F_nu . S, whose face
 //      gradients come from Green-Gauss over the face's diamond (the two
 //      cell centres and the two face nodes, node values the mean of the four
-//      cells around the node);
+//      cells around the node).  W and H leave a thread for each of the
+//      (W + 1) H i-faces and of the W (H + 1) j-faces, edges included: two
+//      passes (with 64 x 4 cells two of the four waves had an edge to form in
+//      a third pass, which the others waited for);
 //   3. each cell sums its four faces, updates its state (the stage kinds of
 //      the Euler kernel) and adds to the tile's partials.
-// Bound by VALU issue (1105 instructions per cell-stage, 45% of the issue
-// slots) and by the latency of a slab's loads.  With one load wait per slab
-// instead of six, no separate pass for the primitives and the cell centres
-// and the node differences formed directly, a stage of the 524,288-cell grid
-// takes 37 us (53 us, 1520 instructions before).  The viscous flux is nearer
-// to extended precision than with node values and centres (9e-15 against
-// 1.9e-14 of the momentum flux on that grid: fewer roundings of sums whose
-// differences matter).
 // Two barriers per slab.  What the update needs of the slab's LDS (volume,
 // own state) is read before the second one, so a wave may stage the next slab
 // while others still update.
+// Bound by VALU issue (about 970 instructions per cell-stage, half of the issue
+// slots) and by the latency of a slab's loads.  A stage of the 524,288-cell grid
+// takes 29 us; 53 us with 64 x 4 slabs staged in six dependent load rounds, 37
+// us with all loads of those slabs at once.  Tiles on a block's faces, whose
+// ghosts take a chain of lookups, go first in each XCD's part of the list and
+// read their face rules with scalar loads: 97 us a step against 130 with 16 x
+// 15 slabs in grid order, where the last tiles to start were such ones.
+// The viscous flux is nearer to extended precision than with node values and
+// centres (9e-15 against 1.9e-14 of the momentum flux on that grid: fewer
+// roundings of sums whose differences matter).
 // Readings of the viscous flux: Stokes's hypothesis with constant mu;
 // Theta = tau u + (mu/Pr) gamma/(gamma-1) grad(p/rho); ghost-cell centres
 // across block links are the neighbour's, across periodic faces the image
@@ -47,27 +50,26 @@ namespace fvk {
 
 namespace {
 
-constexpr int kNsThreads = 256;
-constexpr int kNsRows = 4;          // rows per slab (4 x 64 cells, one per thread)
-constexpr int kQW = 64 + 4;         // state columns i0-2 .. i0+65
-constexpr int kQH = kNsRows + 4;    // state rows j0-2 .. j0+5
-constexpr int kWW = 64 + 2;         // primitive / centre columns i0-1 .. i0+64
-constexpr int kWH = kNsRows + 2;    // rows j0-1 .. j0+4
-constexpr int kNW = 64 + 3;         // node columns i0-1 .. i0+65
-
-// 53 KB per workgroup: three workgroups per CU, as many as their registers
-// allow.
+// The arrays hold a slab of any shape the host may choose (kNsQ ...): cell
+// (r, c) counted from the halo's corner at r (W + 4) + c, its primitives at
+// r (W + 2) + c and nodes at r (W + 3) + c counted from the ring's, i-face
+// (r, c) at r (W + 1) + c, j-face (r, c) at r W + c.  48 KB per workgroup: three
+// workgroups per CU, as many as their registers allow.
 struct NsLds {
-  double q[4][kQH][kQW];             // conserved state of the slab and its halo
-  double w[3][kWH][kWW];             // u, v, p/rho of the slab and one ring
-  double nx[kNsRows + 3][kNW], ny[kNsRows + 3][kNW];  // nodes of the slab and one ring
-                                                    // (rows j0-1.., columns i0-1..)
-  double fi[4][kNsRows][65];         // i-face fluxes (times area, minus viscous)
-  double fj[4][kNsRows][64];         // j-face fluxes at j-1/2 of each row
-  double gi[2][2][kNsRows];          // centres of the ghosts beyond i-min, i-max: [side][x, y]
-  double gj[2][2][64];               // and beyond j-min, j-max
-  double red[4][8];                  // per-wave partials
+  double q[4][kNsQ];            // conserved state of the slab and its halo
+  double w[3][kNsW];            // u, v, p/rho of the slab and one ring
+  double nx[kNsN], ny[kNsN];    // nodes of the slab and one ring
+  double f[2][4][kNsThreads];   // i- and j-face fluxes (times area, minus viscous)
+  double g[2][kNsThreads];      // x, y of the centres of the ghosts beyond i-min and
+                                // i-max (H each), j-min and j-max (W each)
+  double red[4][8];             // per-wave partials
 };
+
+// x / p for 0 <= x < 1024 and 1 <= p <= 1024 by the reciprocal of p, which errs
+// by less than the distance of any quotient here to the next integer
+__device__ __forceinline__ int quot(int x, int p) {
+  return (int)((float)x * (__builtin_amdgcn_rcpf((float)p) * 1.000001f));
+}
 
 // node (i, j) of block B: stored coordinates, or the uniform lattice
 __device__ __forceinline__ void node_of(const DevBlock& B, int i, int j, double& x, double& y) {
@@ -241,54 +243,45 @@ __device__ void ns_centre(const DevBlock* __restrict__ blocks, const DevBlock& B
   }
 }
 
-// Where a line of cells beyond one face (or inside the block) is read from,
-// without touching memory: a row j of B (columns inside), or a column i (rows
-// inside).  kind 0 copy, 1 inflow state, 2 slip mirror, 3 no-slip mirror of
-// face f; p is the line's first cell, vs the variable stride, st the stride
-// along the line.
-struct NsLine {
-  const double* p;
+// The rule of one face of B and the block its ghosts are copied from, read
+// with scalar loads once per slab; lanes select among the four.  An inflow
+// face copies from the block's record: every ghost is the cell at u.
+struct NsFace {
+  const double* u;
   long long vs;
-  int st, kind, f;
+  int kind, ni, nj;
 };
-
-__device__ __forceinline__ NsLine ns_line(const DevBlock* __restrict__ blocks, const DevBlock& B, int buf,
-                                          int d, int x) {
-  const DevBlock* S = &B;
-  const int n0 = d == 0 ? B.ni : B.nj;
-  NsLine L;
-  L.kind = 0;
-  L.f = 0;
-  int along = x;
-  if (x < 0 || x >= n0) {
-    const int side = x < 0 ? 0 : 1, g = side == 0 ? -x : x - n0 + 1;
-    L.f = 2 * d + side;
-    const int bk = B.bc_kind[L.f];
-    if (bk == BC_BLOCK) S = &blocks[B.bc_nbr[L.f]];
-    const int n = d == 0 ? S->ni : S->nj;
-    if (bk == BC_PERIODIC || bk == BC_BLOCK) along = side == 0 ? n - g : g - 1;
-    else if (bk == BC_SLIPWALL || bk == BC_NOSLIP) along = side == 0 ? g - 1 : n - g;
-    else along = side == 0 ? 0 : n - 1;  // EXTRAP, or INFLOW (any valid line)
-    L.kind = bk == BC_INFLOW ? 1 : (bk == BC_SLIPWALL ? 2 : (bk == BC_NOSLIP ? 3 : 0));
-  }
-  L.p = S->u[buf] + (d == 0 ? (long long)along : (long long)along * S->ni);
-  L.vs = S->ncell;
-  L.st = d == 0 ? S->ni : 1;
-  return L;
+__device__ __forceinline__ NsFace ns_face(const DevBlock* __restrict__ blocks, const DevBlock& B, int buf,
+                                          int f) {
+  NsFace F;
+  F.kind = B.bc_kind[f];
+  const DevBlock& S = F.kind == BC_BLOCK ? blocks[B.bc_nbr[f]] : B;
+  F.ni = S.ni;
+  F.nj = S.nj;
+  F.u = F.kind == BC_INFLOW ? B.bc_q[f] : S.u[buf];
+  F.vs = F.kind == BC_INFLOW ? 1 : S.ncell;
+  return F;
+}
+__device__ __forceinline__ NsFace sel_face(bool c, const NsFace& a, const NsFace& b) {
+  NsFace F;
+  F.u = c ? a.u : b.u;
+  F.vs = c ? a.vs : b.vs;
+  F.kind = c ? a.kind : b.kind;
+  F.ni = c ? a.ni : b.ni;
+  F.nj = c ? a.nj : b.nj;
+  return F;
 }
 
-// the rule of a line's cell at index t along it, applied to the copied state
-__device__ __forceinline__ void ns_fix(const NsLine& L, const DevBlock& B, int t, double* q) {
-  if (L.kind == 1) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) q[v] = B.bc_q[L.f][v];
-  } else if (L.kind == 2) {
-    double sx, sy;
-    wall_vec(B, L.f, t, sx, sy);
-    slip_mirror(q, sx, sy);
-  } else if (L.kind == 3) {
-    noslip_mirror<2>(q, B.bc_q[L.f]);
-  }
+// the ghost (x = i or j outside by g on `side` of direction d, t the index
+// along the face) of face F: its place in the source block
+__device__ __forceinline__ const double* ns_ghost(const NsFace& F, int d, int side, int g, int t) {
+  const int n = d == 0 ? F.ni : F.nj;
+  int along;
+  if (F.kind == BC_PERIODIC || F.kind == BC_BLOCK) along = side == 0 ? n - g : g - 1;
+  else if (F.kind == BC_EXTRAP) along = side == 0 ? 0 : n - 1;
+  else along = side == 0 ? g - 1 : n - g;  // SLIPWALL, NOSLIP
+  const long long o = d == 0 ? (long long)t * F.ni + along : (long long)along * F.ni + t;
+  return F.u + (F.kind == BC_INFLOW ? 0 : o);
 }
 
 template <int LIM, typename T>
@@ -316,11 +309,10 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
   using SK = StageKind<MODE>;
   constexpr int bin = SK::bin;
   constexpr int bout = SK::bout;
-  const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int lane = tid & 63;
+  int tid = threadIdx.x;
   int blk = tl.blk;
   if (MODE != 0 && I.stopped) return;
-  const int i0 = tl.i0, nc = tl.ncol;
+  const int i0 = tl.i0, nc = tl.ncol, H = tl.ny;
   Recon<T> rc;
   rc.lim = I.limiter;
   rc.heps = T(0.5 * I.eps);
@@ -339,163 +331,158 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
   int bad = 0;
 
 #pragma unroll 1
-  for (int js = tl.j0; js < tl.j0 + tl.n; js += kNsRows) {
-    // what depends on the lane and the block's descriptor is formed per slab:
+  for (int js = tl.j0; js < tl.j0 + tl.n; js += H) {
+    // what depends on the thread and the block's descriptor is formed per slab:
     // hoisted out of this loop it would not fit the registers
-    asm volatile("" : "+v"(lane), "+s"(blk));
+    asm volatile("" : "+v"(tid), "+s"(blk));
     const DevBlock& B = blocks[blk];
-    const int ni = B.ni;
+    const int ni = B.ni, nj = B.nj;
     const long long ncell = B.ncell;
-    // the slab row of this wave: turned with the tile, so that the wave that
-    // also forms the top edge is not always on the same SIMD
-    const int wrow = (wv + tl.local) & (kNsRows - 1);
-    const bool act_i = lane < nc;
-    const int ic = act_i ? i0 + lane : ni - 1;  // own column (idle lanes: a valid one)
-    const int icn = min(i0 + lane, ni);         // own node column
-    const int nj = B.nj;
     const bool curv = B.xn != nullptr;
-    // halo columns i0-2, i0-1, i0+nc, i0+nc+1: lane = 4 * row + which, in wave 1
-    const bool hwave = wv == 1;
-    const int hc = lane & 3, hrow = lane >> 2;
-    const int hcol = hc < 2 ? hc : nc + hc;     // its LDS column
     const bool lo_edge = i0 == 0, hi_edge = i0 + nc == ni;
-    const int nr = min(kNsRows, tl.j0 + tl.n - js);
+    const int nr = min(H, tl.j0 + tl.n - js);
+    const int qp = nc + 4, wp = nc + 2, np = nc + 3, fp = nc + 1;  // pitches
+    const int lj = quot(tid, nc), li = tid - lj * nc;               // own cell
+    const bool act = lj < nr;
     // ---- 1. every load of the slab, then the ghost rules, then LDS
-    double qs[2][4], xs[2], ys[2], qh[4], xh = 0.0, yh = 0.0;
-    NsLine ln[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {  // rows js-2+wv and js+2+wv of the own column
-      const int r = wv + 4 * h;
-      ln[h].kind = 0;
-      if (r < nr + 4) {
-        ln[h] = ns_line(blocks, B, bin, 1, js - 2 + r);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) qs[h][v] = ldg(ln[h].p + v * ln[h].vs + ic);
-      }
-      if (r < nr + 3) node_of(B, icn, min(max(js - 1 + r, 0), nj), xs[h], ys[h]);
+    const bool inside = i0 >= 2 && i0 + nc + 2 <= ni && js >= 2 && js + nr + 2 <= nj;
+    NsFace F0{}, F1{}, F2{}, F3{};
+    if (!inside) {
+      F0 = ns_face(blocks, B, bin, 0);
+      F1 = ns_face(blocks, B, bin, 1);
+      F2 = ns_face(blocks, B, bin, 2);
+      F3 = ns_face(blocks, B, bin, 3);
     }
-    NsLine lh;
-    lh.kind = 0;
-    const int hj = js - 2 + hrow;  // row of the halo cell
-    const bool hcell = hwave && hrow < nr + 4;
-    const bool hin = hj >= 0 && hj < nj;
-    if (hcell) {
-      // the four columns are the same for the whole wave: scalar sources
-      const NsLine l0 = ns_line(blocks, B, bin, 0, i0 - 2), l1 = ns_line(blocks, B, bin, 0, i0 - 1);
-      const NsLine l2 = ns_line(blocks, B, bin, 0, i0 + nc), l3 = ns_line(blocks, B, bin, 0, i0 + nc + 1);
-      lh.p = hc == 0 ? l0.p : (hc == 1 ? l1.p : (hc == 2 ? l2.p : l3.p));
-      lh.vs = hc == 0 ? l0.vs : (hc == 1 ? l1.vs : (hc == 2 ? l2.vs : l3.vs));
-      lh.st = hc == 0 ? l0.st : (hc == 1 ? l1.st : (hc == 2 ? l2.st : l3.st));
-      lh.kind = hc == 0 ? l0.kind : (hc == 1 ? l1.kind : (hc == 2 ? l2.kind : l3.kind));
-      lh.f = hc == 0 ? l0.f : (hc == 1 ? l1.f : (hc == 2 ? l2.f : l3.f));
-      const double* p = lh.p + (long long)min(max(hj, 0), nj - 1) * lh.st;
+    double qs[2][4], xs[2], ys[2];
+    // per cell: -1 none, 0 copied, 4 a corner, else 8 + face whose wall mirrors it
+    int sr[2], sc[2], rule[2];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) qh[v] = ldg(p + v * lh.vs);
-      // node columns i0-1, i0+nc and i0+nc+1
-      if (hc > 0 && hrow < nr + 3)
-        node_of(B, hc == 1 ? max(i0 - 1, 0) : min(i0 + nc + hc - 2, ni), min(max(js - 1 + hrow, 0), nj),
-                xh, yh);
-    }
-    // centres of the ghosts beyond the block's faces (boundary tiles only)
-    if (mu > 0.0) {
-      if (wv == 2 && (lo_edge || hi_edge) && lane < 2 * kNsRows) {
-        const int side = lane >> 2, r = lane & 3;
-        if (r < nr && (side == 0 ? lo_edge : hi_edge)) {
-          double cx, cy;
-          ns_centre(blocks, B, side == 0 ? -1 : ni, js + r, cx, cy);
-          L.gi[side][0][r] = cx;
-          L.gi[side][1][r] = cy;
+    for (int h = 0; h < 2; ++h) {
+      const int x = tid + h * kNsThreads;
+      sr[h] = quot(x, qp);
+      sc[h] = x - sr[h] * qp;
+      rule[h] = -1;
+      if (sr[h] < nr + 4) {
+        const int i = i0 - 2 + sc[h], j = js - 2 + sr[h];
+        rule[h] = 0;
+        const double* p = B.u[bin] + (long long)j * ni + i;
+        long long vs = ncell;
+        if (!inside) {
+          const bool iin = i >= 0 && i < ni, jin = j >= 0 && j < nj;
+          if (!iin && !jin) {
+            rule[h] = 4;  // both rules, below
+          } else if (!iin || !jin) {
+            const int d = iin ? 1 : 0, y = iin ? j : i, n0 = iin ? nj : ni;
+            const int side = y < 0 ? 0 : 1;
+            const NsFace F = sel_face(d == 0, sel_face(side == 0, F0, F1), sel_face(side == 0, F2, F3));
+            p = ns_ghost(F, d, side, side == 0 ? -y : y - n0 + 1, iin ? i : j);
+            vs = F.vs;
+            if (F.kind == BC_SLIPWALL || F.kind == BC_NOSLIP) rule[h] = 8 + 2 * d + side;
+          }
+        }
+        if (rule[h] != 4) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) qs[h][v] = ldg(p + v * vs);
         }
       }
-      if (((wv == 0 && js == 0) || (wv == 3 && js + nr == nj)) && act_i) {
-        const int side = wv == 0 ? 0 : 1;
+    }
+    int nn[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int x = tid + h * kNsThreads, r = quot(x, np);
+      nn[h] = r < nr + 3 ? x : -1;
+      // (clamped into the block: ring nodes outside it are not used)
+      if (nn[h] >= 0)
+        node_of(B, min(max(i0 - 1 + x - r * np, 0), ni), min(max(js - 1 + r, 0), nj), xs[h], ys[h]);
+    }
+    // centres of the ghosts beyond the block's faces (boundary tiles only)
+    if (mu > 0.0 && !inside && tid < 2 * (nr + nc)) {
+      const bool di = tid < 2 * nr;
+      const int y = di ? tid : tid - 2 * nr, n = di ? nr : nc;
+      const int side = y >= n ? 1 : 0, t = y - side * n;
+      if (di ? (side == 0 ? lo_edge : hi_edge) : (side == 0 ? js == 0 : js + nr == nj)) {
         double cx, cy;
-        ns_centre(blocks, B, i0 + lane, side == 0 ? -1 : nj, cx, cy);
-        L.gj[side][0][lane] = cx;
-        L.gj[side][1][lane] = cy;
+        ns_centre(blocks, B, di ? (side == 0 ? -1 : ni) : i0 + t, di ? js + t : (side == 0 ? -1 : nj), cx,
+                  cy);
+        L.g[0][tid] = cx;
+        L.g[1][tid] = cy;
       }
     }
-    // u, v, p/rho of a staged cell
-    auto put_cell = [&](const double* q, int r, int c) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) L.q[v][r][c] = q[v];
+    for (int h = 0; h < 2; ++h) {
+      if (rule[h] < 0) continue;
+      const int r = sr[h], c = sc[h];
+      double* q = qs[h];
+      if (rule[h] == 4) {
+        ns_cell(blocks, &B, bin, i0 - 2 + c, js - 2 + r, q);
+      } else if (rule[h] >= 8) {
+        const int f = rule[h] - 8;
+        const int kind = f == 0 ? F0.kind : (f == 1 ? F1.kind : (f == 2 ? F2.kind : F3.kind));
+        if (kind == BC_SLIPWALL) {
+          double sx, sy;
+          wall_vec(B, f, f < 2 ? js - 2 + r : i0 - 2 + c, sx, sy);
+          slip_mirror(q, sx, sy);
+        } else {
+          noslip_mirror<2>(q, B.bc_q[f]);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) L.q[v][tid + h * kNsThreads] = q[v];
       if (r >= 1 && r <= nr + 2 && c >= 1 && c <= nc + 2) {
         const double ir = M<double>::rcp(q[0]);
         const double u = q[1] * ir, v = q[2] * ir;
         const double p = (gamma - 1.0) * (q[3] - 0.5 * q[0] * (u * u + v * v));
-        L.w[0][r - 1][c - 1] = u;
-        L.w[1][r - 1][c - 1] = v;
-        L.w[2][r - 1][c - 1] = p * ir;
+        const int x = (r - 1) * wp + c - 1;
+        L.w[0][x] = u;
+        L.w[1][x] = v;
+        L.w[2][x] = p * ir;
       }
-    };
+    }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int r = wv + 4 * h;
-      if (r < nr + 4 && act_i) {
-        if (ln[h].kind != 0) ns_fix(ln[h], B, ic, qs[h]);
-        put_cell(qs[h], r, lane + 2);
+    for (int h = 0; h < 2; ++h)
+      if (nn[h] >= 0) {
+        L.nx[nn[h]] = xs[h];
+        L.ny[nn[h]] = ys[h];
       }
-      if (r < nr + 3 && act_i) {
-        L.nx[r][lane + 1] = xs[h];
-        L.ny[r][lane + 1] = ys[h];
-      }
-    }
-    if (hcell) {
-      if (!hin) ns_cell(blocks, &B, bin, i0 - 2 + hcol, hj, qh);  // a corner: both rules
-      else if (lh.kind != 0) ns_fix(lh, B, hj, qh);
-      put_cell(qh, hrow, hcol);
-      if (hc > 0 && hrow < nr + 3) {
-        const int c = hc == 1 ? 0 : nc + hc - 1;
-        L.nx[hrow][c] = xh;
-        L.ny[hrow][c] = yh;
-      }
-    }
     __syncthreads();
 
-    // ---- 2. face fluxes, one thread per cell: its left and bottom faces
-    const int li = lane, lj = wrow;
-    const bool act = act_i && lj < nr;
-    const long long ro = (long long)(js + lj) * ni + ic;
-    double un[4] = {0, 0, 0, 0};
+    // ---- 2. face fluxes, one face per thread and pass
+    const long long ro = (long long)(js + lj) * ni + i0 + li;
+    double un[4] = {0, 0, 0, 0}, qin[4];
     if constexpr (SK::reads_un) {  // used after the fluxes
       if (act) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) un[v] = ldg(B.u[0] + v * ncell + ro);
       }
     }
-    // The faces of a wave, one face per lane and pass: its row's i-faces, for
-    // the slab's first row the right edge (one row per lane), its row's
-    // j-faces, and for the slab's last row the top edge.  Both directions run the
-    // same code with the strides of their normal (n) and of the way from
-    // node A to node B of the face (t): unrolled per direction, the passes
-    // overlap and their registers spill.
-    double Fo[4] = {0, 0, 0, 0}, qin[4];
+    // Both directions run the same code with the strides of their normal (n)
+    // and of the way from node A to node B of the face (t): unrolled, the
+    // passes overlap and their registers spill.
 #pragma unroll 1
-    for (int pass = 0; pass < 4; ++pass) {
-      if (pass == 1 && lj != 0) continue;
-      if (pass == 3 && lj != nr - 1) break;
-      const bool di = pass < 2;                                 // i-faces
-      const int fr = pass == 1 ? lane : (pass == 3 ? nr : lj);  // face row
-      const int fc = pass == 1 ? nc : lane;                     // face column
-      if (pass == 1 ? lane >= nr : !act) continue;
-      const int sq = di ? 1 : kQW;
-      const double* q = di ? &L.q[0][fr + 2][fc] : &L.q[0][fr][fc + 2];
+    for (int d = 0; d < 2; ++d) {
+      const bool di = d == 0;                 // i-faces
+      const int pf = di ? fp : nc;
+      const int fr = quot(tid, pf), fc = tid - fr * pf;
+      if (fr >= (di ? nr : nr + 1)) continue;
+      const int sq = di ? 1 : qp;
+      const double* q = &L.q[0][(fr + (di ? 2 : 0)) * qp + fc + (di ? 0 : 2)];
       double c0[4], c1[4], c2[4], c3[4];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        c0[v] = q[v * kQH * kQW];
-        c1[v] = q[v * kQH * kQW + sq];
-        c2[v] = q[v * kQH * kQW + 2 * sq];
-        c3[v] = q[v * kQH * kQW + 3 * sq];
+        c0[v] = q[v * kNsQ];
+        c1[v] = q[v * kNsQ + sq];
+        c2[v] = q[v * kNsQ + 2 * sq];
+        c3[v] = q[v * kNsQ + 3 * sq];
       }
       // nodes A and B: the area vector is B - A turned by -90 degrees (on a
       // uniform block exactly the axis times the spacing)
-      const int A = di ? (fr + 1) * kNW + fc + 1 : (fr + 1) * kNW + fc + 2;
-      const int t = di ? kNW : -1, n = di ? 1 : kNW;
-      const double* X = &L.nx[0][0] + A;
-      const double* Y = &L.ny[0][0] + A;
+      const int A = (fr + 1) * np + fc + (di ? 1 : 2);
+      const int t = di ? np : -1, n = di ? 1 : np;
+      const double* X = L.nx + A;
+      const double* Y = L.ny + A;
       const double Sx = curv ? Y[t] - Y[0] : (di ? B.area[0] : 0.0);
       const double Sy = curv ? -(X[t] - X[0]) : (di ? 0.0 : B.area[1]);
+      double Fo[4];
       T G[4];
       inv_flux<LIM, T>(rc, K, c0, c1, c2, c3, Sx, Sy, G);
 #pragma unroll
@@ -503,12 +490,12 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
       if (mu > 0.0) {
         // difference between the nodes' values: the face's own two cells
         // cancel, a quarter of the cells beside them is left
-        const int tw = di ? kWW : -1, nw = di ? 1 : kWW;
-        const double* w = di ? &L.w[0][fr + 1][fc] : &L.w[0][fr][fc + 1];
+        const int tw = di ? wp : -1, nw = di ? 1 : wp;
+        const double* w = &L.w[0][(fr + (di ? 1 : 0)) * wp + fc + (di ? 0 : 1)];
         double wL[3], wR[3], wt[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          const double* wk = w + k * kWH * kWW;
+          const double* wk = w + k * kNsW;
           wL[k] = wk[0];
           wR[k] = wk[nw];
           wt[k] = 0.25 * ((wk[tw] + wk[nw + tw]) - (wk[-tw] + wk[nw - tw]));
@@ -523,8 +510,8 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
           const int m = lo ? n : -n;
           const double cx = 0.25 * ((X[0] + X[t]) + (X[m] + X[t + m]));
           const double cy = 0.25 * ((Y[0] + Y[t]) + (Y[m] + Y[t + m]));
-          const double* gc = di ? &L.gi[lo ? 0 : 1][0][fr] : &L.gj[lo ? 0 : 1][0][fc];
-          const double gx = gc[0], gy = gc[di ? kNsRows : 64];
+          const int y = di ? (lo ? 0 : nr) + fr : 2 * nr + (lo ? 0 : nc) + fc;
+          const double gx = L.g[0][y], gy = L.g[1][y];
           dx = lo ? cx - gx : gx - cx;
           dy = lo ? cy - gy : gy - cy;
         }
@@ -533,27 +520,24 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
 #pragma unroll
         for (int v = 0; v < 4; ++v) Fo[v] -= (double)Fv[v];
       }
-      if (pass != 3) {  // (the top edge stays in the registers of its row)
-        double* F = di ? &L.fi[0][fr][fc] : &L.fj[0][fr][fc];
-        const int sv = di ? kNsRows * 65 : kNsRows * 64;
 #pragma unroll
-        for (int v = 0; v < 4; ++v) F[v * sv] = Fo[v];
-      }
+      for (int v = 0; v < 4; ++v) L.f[d][v][tid] = Fo[v];
     }
+    // own state, and the nodes of the own cell (0.5 times the sums of opposite
+    // ones are its mean area vectors)
     double vol = B.vol;
-    if (act) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) qin[v] = L.q[v][lj + 2][li + 2];
-    }
-    // nodes of the own cell (0.5 times the sums of opposite ones are its
-    // mean area vectors)
     double xa = 0, ya = 0, xb = 0, yb = 0, xc = 0, yc = 0, xd = 0, yd = 0;
-    if (curv && act) {
-      xa = L.nx[lj + 1][li + 1], ya = L.ny[lj + 1][li + 1];
-      xb = L.nx[lj + 1][li + 2], yb = L.ny[lj + 1][li + 2];
-      xc = L.nx[lj + 2][li + 1], yc = L.ny[lj + 2][li + 1];
-      xd = L.nx[lj + 2][li + 2], yd = L.ny[lj + 2][li + 2];
-      vol = 0.5 * fmad(xd - xa, yc - yb, -((xc - xb) * (yd - ya)));
+    if (act) {
+      const int x = (lj + 2) * qp + li + 2;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) qin[v] = L.q[v][x];
+      if (curv) {
+        const double* X = L.nx + (lj + 1) * np + li + 1;
+        const double* Y = L.ny + (lj + 1) * np + li + 1;
+        xa = X[0], ya = Y[0], xb = X[1], yb = Y[1];
+        xc = X[np], yc = Y[np], xd = X[np + 1], yd = Y[np + 1];
+        vol = 0.5 * fmad(xd - xa, yc - yb, -((xc - xb) * (yd - ya)));
+      }
     }
     double Sb[2][3];
     if constexpr (SK::cfl) {
@@ -567,12 +551,11 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
 
     // ---- 3. residual, update, partials
     if (act) {
+      const int f = lj * fp + li;
       double R[4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const double ft = lj == nr - 1 ? Fo[v] : L.fj[v][lj + 1][li];
-        R[v] = (0.0 + (L.fi[v][lj][li + 1] - L.fi[v][lj][li])) + (ft - L.fj[v][lj][li]);
-      }
+      for (int v = 0; v < 4; ++v)
+        R[v] = (0.0 + (L.f[0][v][f + 1] - L.f[0][v][f])) + (L.f[1][v][tid + nc] - L.f[1][v][tid]);
       const double iv = M<double>::rcp(vol);
       if (B.src != nullptr) {  // the source part of Eq. (residual): - |Omega| S_h
 #pragma unroll
@@ -586,14 +569,14 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
           nacc[v] = fmad(rv, rv, nacc[v]);
         }
       } else {
-        const double f = dt * iv;
+        const double f1 = dt * iv;
         double out[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           if constexpr (SK::low) {
-            out[v] = fmad(-f, R[v], un[v]);
+            out[v] = fmad(-f1, R[v], un[v]);
           } else {
-            const double us = fmad(-f, R[v], qin[v]);
+            const double us = fmad(-f1, R[v], qin[v]);
             if (MODE == 1) out[v] = us;
             else if (MODE == 2) out[v] = fmad(0.75, un[v], 0.25 * us);
             else out[v] = fmad(1.0 / 3.0, un[v], (2.0 / 3.0) * us);
@@ -616,6 +599,7 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
   // ---- per-tile partials: fixed-order wave reductions, then the four waves
   double* part = I.part + tl.local;
   const long long ps = I.ntiles;
+  const int lane = tid & 63, wv = tid >> 6;
   if (MODE == 0 || MODE == 1) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {

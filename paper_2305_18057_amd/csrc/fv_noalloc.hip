@@ -98,7 +98,7 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
     if (tune_lookup(tune_path(nullptr), tune_key(hg, p->precision, ns), tsh)) sh = tsh;
   }
   std::vector<fvk::DevTile> htiles;
-  build_tiles(hg, sh, 0, 0, htiles);
+  build_tiles(hg, sh, 0, 0, htiles, ns);
   // the list of low tiles can be longer than reserved above: taller ones where
   // the scratch has no room for it
   while ((long long)htiles.size() > L.max_tiles) {
@@ -109,7 +109,7 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
     }
     if (sh.rows >= 64) break;
     sh.rows *= 2;
-    build_tiles(hg, sh, 0, 0, htiles);
+    build_tiles(hg, sh, 0, 0, htiles, ns);
   }
   const int nt = (int)htiles.size();
   if (nt > L.max_tiles) return set_error(FV_E_INVAL, "tile list exceeds its capacity");

@@ -81,11 +81,13 @@ void build_segs(const HostGrid& g, std::vector<fvk::GhostSeg>& segs);
 void pack_nodes(const HostGrid& g, char* dst);
 hipError_t upload_nodes(const HostGrid& g, char* dst, hipStream_t s);
 void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int block_index_offset,
-                 std::vector<fvk::DevTile>& out);
+                 std::vector<fvk::DevTile>& out, bool ns = false);
 // ns: for the Navier-Stokes stage kernel; shared: beside other instances of a server
 TileShape default_shape(const HostGrid& g, bool ns, bool shared = false);
 // columns and rows of the general 3D kernel's tiles of an ni x nj block
 void gen_tile_shape(int ni, int nj, int& w, int& h);
+// columns and slab rows of the Navier-Stokes kernel's tiles of n rows
+void ns_tile_shape(int ni, int n, int& w, int& h);
 int size_class(const HostGrid& g);
 
 // autotune table (JSON file of "key": {"rows": r, "ny": y})

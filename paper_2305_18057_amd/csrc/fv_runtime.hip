@@ -163,20 +163,21 @@ int validate_and_copy(const fv_grid_desc* d, HostGrid& g) {
 
 static const int kMinRows2D = 1, kMinPlanes3D = 1, kMinNy3D = 3;
 
-// Every split of the columns into even parts, with the most rows for which
-// one thread each is enough for the (W + 1) H i-faces, the W (H + 1) j-faces
-// and the 4 (W + H) halo cells of a plane.  The fewest tiles win (a plane of
-// a tile costs the same three flux passes however many threads are idle),
-// with 0.4% for each halo row or column.
-void gen_tile_shape(int ni, int nj, int& w, int& h) {
-  constexpr int N = fvk::kGenThreads;
+// Tile cross-sections of the kernels that take a cell per thread.  Every split
+// of the ni columns into even parts, with the most rows for which one thread
+// each is enough for the (W + 1) H and the W (H + 1) faces of the two
+// directions and `fits` holds; the rows split evenly too.  The fewest parts win
+// (one costs the same flux passes however many threads are idle), with 0.4%
+// for each halo row or column.
+template <class Fits>
+static void best_section(int ni, int nj, int threads, int wmax, Fits fits, int& w, int& h) {
   double best = 0.0;
   w = h = 0;
-  for (int x = std::min(ni, 60); x >= 1; --x) {
+  for (int x = std::min(ni, wmax); x >= 1; --x) {
     const int nt = (ni + x - 1) / x, W = (ni + nt - 1) / nt;
     if (W != x) continue;  // the even split of another column count
-    int H = std::min({nj, N / (W + 1), N / W - 1, N / 4 - W, fvk::kGenQ / (W + 4) - 4,
-                      fvk::kGenNd / (W + 1) - 1});
+    int H = std::min({nj, threads / (W + 1), threads / W - 1});
+    while (H > 0 && !fits(W, H)) --H;
     if (H < 1) continue;
     const int nh = (nj + H - 1) / H;
     H = (nj + nh - 1) / nh;
@@ -189,6 +190,23 @@ void gen_tile_shape(int ni, int nj, int& w, int& h) {
   }
 }
 
+void gen_tile_shape(int ni, int nj, int& w, int& h) {
+  // one thread per halo cell
+  best_section(ni, nj, fvk::kGenThreads, 60, [](int W, int H) {
+    return 4 * (W + H) <= fvk::kGenThreads && (W + 4) * (H + 4) <= fvk::kGenQ &&
+           (W + 1) * (H + 1) <= fvk::kGenNd;
+  }, w, h);
+}
+
+void ns_tile_shape(int ni, int n, int& w, int& h) {
+  // two threads' cells and nodes, one thread per ghost centre (never more tiles
+  // than 64 columns by one row make)
+  best_section(ni, n, fvk::kNsThreads, 64, [](int W, int H) {
+    return (W + 4) * (H + 4) <= fvk::kNsQ && (W + 2) * (H + 2) <= fvk::kNsW &&
+           (W + 3) * (H + 3) <= fvk::kNsN && 2 * (W + H) <= fvk::kNsThreads;
+  }, w, h);
+}
+
 // rows, planes: the least rows of a 2D tile, planes of a 3D one
 static long long max_tiles_of(const HostGrid& g, int rows, int planes) {
   long long t = 0;
@@ -196,6 +214,17 @@ static long long max_tiles_of(const HostGrid& g, int rows, int planes) {
     const long long ci = (B.ni + 63) / 64;
     if (g.ndim == 2) t += ci * ((B.nj + rows - 1) / rows);
     else t += ci * ((B.nj + kMinNy3D - 1) / kMinNy3D) * ((B.nk + planes - 1) / planes);
+  }
+  return t;
+}
+
+static long long ns_tiles(const HostGrid& g, int rows) {
+  long long t = 0;
+  for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
+    const fv_block_desc& B = g.blocks[b];
+    int w, h;
+    ns_tile_shape(B.ni, std::min(B.nj, rows), w, h);
+    t += (long long)((B.ni + w - 1) / w) * ((B.nj + rows - 1) / rows);
   }
   return t;
 }
@@ -386,7 +415,7 @@ static double model_us(const RoundModel& M, long long tiles, int n) {
 // 32 tiles (43 us, now 33); 256^3 in five rounds where three taller ones do.
 TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
   TileShape s;
-  if (shared) {
+  if (shared && !ns) {
     if (g.ndim == 2) {
       // aim for about 8 wavefronts per SIMD across the chip, 4..64 rows
       const long long want = g.ncells / (64LL * 8192);
@@ -413,13 +442,20 @@ TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
     return t;
   };
   if (g.ndim == 2 && ns) {
-    // slabs of 4 rows, and twice as many while eight tiles per CU are left: the
-    // three workgroups of a CU drift apart and fill each other's waits, so
-    // even rounds matter less than a short tail (524 k cells: 117, 123, 123 and
-    // 134 us a step with 4, 8, 12 and 16 rows; 1.05 M: 214, 204, 211, 218)
-    s.rows = 4;
+    // one slab, and twice as many while eight tiles per CU are left: the three
+    // workgroups of a CU drift apart and fill each other's waits, so even
+    // rounds matter less than a short tail (524 k cells in slabs of 4 rows: 117,
+    // 123, 123 and 134 us a step with 4, 8, 12 and 16 rows; 1.05 M: 214, 204,
+    // 211, 218)
+    s.rows = 1;
     s.ny = 1;
-    while (s.rows < 64 && tiles_of(2 * s.rows, 1) >= 8LL * device_cu_count()) s.rows *= 2;
+    for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
+      int w, h;
+      ns_tile_shape(g.blocks[b].ni, g.blocks[b].nj, w, h);
+      s.rows = std::max(s.rows, h);
+    }
+    s.rows = std::min(s.rows, 64);
+    while (2 * s.rows <= 64 && ns_tiles(g, 2 * s.rows) >= 8LL * device_cu_count()) s.rows *= 2;
     return s;
   }
   int nmax = 1;
@@ -449,7 +485,7 @@ TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
 }
 
 void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int boff,
-                 std::vector<fvk::DevTile>& out) {
+                 std::vector<fvk::DevTile>& out, bool ns) {
   out.clear();
   int local = 0;
   for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
@@ -457,19 +493,21 @@ void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int bof
     if (g.ndim == 2) {
       // at most 64 rows: the right-edge fluxes of a tile are formed one row per lane
       const int R = std::min(64, std::max(kMinRows2D, sh.rows));
+      int W = 64, H = 1;
+      if (ns) ns_tile_shape(B.ni, std::min(B.nj, R), W, H);
       for (int j0 = 0; j0 < B.nj; j0 += R)
-        for (int i0 = 0; i0 < B.ni; i0 += 64) {
+        for (int i0 = 0; i0 < B.ni; i0 += W) {
           fvk::DevTile t;
           std::memset(&t, 0, sizeof(t));
           t.blk = b + boff;
           t.inst = inst_index;
           t.local = local++;
-          t.ncol = std::min(64, B.ni - i0);
+          t.ncol = std::min(W, B.ni - i0);
           t.i0 = i0;
           t.j0 = j0;
           t.k0 = 0;
           t.n = std::min(R, B.nj - j0);
-          t.ny = 1;
+          t.ny = H;
           t.curv = B.x != nullptr ? 1 : 0;
           out.push_back(t);
         }
@@ -495,6 +533,19 @@ void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int bof
             out.push_back(t);
           }
     }
+  }
+  if (ns) {
+    // Tiles that touch the block's faces resolve ghosts and take about twice as
+    // long: within each XCD's part of the list they go first, so that none of
+    // them starts last
+    const size_t part = (out.size() + fvk::kXcds - 1) / fvk::kXcds;
+    for (size_t p = 0; p < out.size(); p += part)
+      std::stable_partition(out.begin() + p, out.begin() + std::min(out.size(), p + part),
+                            [&](const fvk::DevTile& t) {
+                              const fv_block_desc& B = g.blocks[t.blk - boff];
+                              return t.i0 < 2 || t.j0 < 2 || t.i0 + t.ncol + 2 > B.ni ||
+                                     t.j0 + t.n + 2 > B.nj;
+                            });
   }
 }
 

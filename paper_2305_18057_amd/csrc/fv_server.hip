@@ -581,7 +581,7 @@ int submit(fv_server* S, const fv_grid_desc* desc, const double* U0, const doubl
   try {
     r->U0.assign(U0, U0 + r->hg.state_size);
     if (src) r->src.assign(src, src + r->hg.state_size);
-    build_tiles(r->hg, sh, 0, 0, r->tiles);
+    build_tiles(r->hg, sh, 0, 0, r->tiles, ns);
   } catch (const std::bad_alloc&) {
     delete r;
     return set_error(FV_E_NOMEM, "host allocation failed");
