@@ -66,8 +66,9 @@ int launch_grid(const LaunchSet& s, int fp32, bool ns = false);
 int enqueue_stage(const StepPlan& P, int mode, int fp32, double* rout, hipStream_t s);
 int enqueue_cfl(const StepPlan& P, hipStream_t s);
 // nsteps full steps; with a cache, replays (and captures on first use) a graph
-// (variant tells apart plans with different launch sets in one cache)
+// (variant tells apart plans with different launch sets in one cache).  host:
+// pinned memory the record of a one-instance plan is left in at the end
 int enqueue_steps(const StepPlan& P, int fp32, int nsteps, hipStream_t s, GraphCache* cache,
-                  int variant = 0);
+                  int variant = 0, fvk::DevInstance* host = nullptr);
 
 }  // namespace fvexec

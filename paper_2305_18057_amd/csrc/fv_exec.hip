@@ -102,28 +102,29 @@ static const int kStages3[] = {1, 2, 3};
 static const int kStages2[] = {1, 6};
 static const int kStages4[] = {1, 4, 5, 6};
 
-static int enqueue_one_step(const StepPlan& P, int fp32, hipStream_t st) {
+static int enqueue_one_step(const StepPlan& P, int fp32, hipStream_t st,
+                            fvk::DevInstance* host = nullptr) {
   const int* modes = P.rk == 2 ? kStages2 : (P.rk == 4 ? kStages4 : kStages3);
   const int ns = P.rk == 2 ? 2 : (P.rk == 4 ? 4 : 3);
   for (int m = 0; m < ns; ++m) {
     const int e = enqueue_stage(P, modes[m], fp32, nullptr, st);
     if (e) return e;
   }
-  const hipError_t e = fvk::launch_finalize(st, P.insts, P.active, P.ninst, P.ninst_dev);
+  const hipError_t e = fvk::launch_finalize(st, P.insts, P.active, P.ninst, P.ninst_dev, host);
   if (e != hipSuccess)
     return fvrt::set_error(FV_E_DEVICE, "finalize launch failed: %s", hipGetErrorString(e));
   return FV_OK;
 }
 
 int enqueue_steps(const StepPlan& P, int fp32, int nsteps, hipStream_t st, GraphCache* cache,
-                  int variant) {
+                  int variant, fvk::DevInstance* host) {
   if (nsteps <= 0) return FV_OK;
   // one step is launched as it is: a graph's launch costs about 25 us more than
   // that of its first kernel, and capturing it about 170 (52 us against 62 for
   // one step of 128 x 64 cells; from two steps on the graph is 10 us faster)
   if (!cache || !graphs_enabled() || nsteps == 1) {
     for (int k = 0; k < nsteps; ++k) {
-      const int e = enqueue_one_step(P, fp32, st);
+      const int e = enqueue_one_step(P, fp32, st, k == nsteps - 1 ? host : nullptr);
       if (e) return e;
     }
     return FV_OK;
@@ -161,6 +162,11 @@ int enqueue_steps(const StepPlan& P, int fp32, int nsteps, hipStream_t st, Graph
   }
   const hipError_t e = hipGraphLaunch(ex, st);
   if (e != hipSuccess) return fvrt::set_error(FV_E_DEVICE, "graph launch failed: %s", hipGetErrorString(e));
+  if (host) {
+    const hipError_t ep = fvk::launch_publish(st, P.insts, host);
+    if (ep != hipSuccess)
+      return fvrt::set_error(FV_E_DEVICE, "publish launch failed: %s", hipGetErrorString(ep));
+  }
   return FV_OK;
 }
 

@@ -344,7 +344,7 @@ static int run_steps(fv_grid* g, const fv_params* p, long long nsteps, double dr
   const bool check = drop_tol > 0.0;
   while (left > 0) {
     const int c = (int)std::min<long long>(left, chunk);
-    st = fvexec::enqueue_steps(g->plan, fp32, c, g->stream, &g->graphs);
+    st = fvexec::enqueue_steps(g->plan, fp32, c, g->stream, &g->graphs, 0, left == c ? g->pin : nullptr);
     if (st) return st;
     left -= c;
     since_check += c;
@@ -355,7 +355,8 @@ static int run_steps(fv_grid* g, const fv_params* p, long long nsteps, double dr
       if (g->hinst.stopped) break;
     }
   }
-  st = get_inst(g);
+  // the last steps have left the record in pinned memory
+  st = nsteps > 0 && left == 0 ? wait_inst(g) : get_inst(g);
   if (st) return st;
   fill_info(g, info);
   if (g->hinst.flags & fvk::FLAG_NONPHYS)

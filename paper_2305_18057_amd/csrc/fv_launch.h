@@ -53,7 +53,7 @@ const void* stage3d_gen_kernel_ptr(int fp32);
 //             host address); complete when the stream is
 hipError_t launch_prepare(hipStream_t s, DevInstance* insts, const int* active, int n);
 hipError_t launch_finalize(hipStream_t s, DevInstance* insts, const int* active, int n,
-                           const int* n_dev = nullptr);
+                           const int* n_dev = nullptr, DevInstance* host = nullptr);
 hipError_t launch_cfl_init(hipStream_t s, DevInstance* insts, const int* active, int n,
                            DevInstance* host = nullptr);
 hipError_t launch_rnorms(hipStream_t s, DevInstance* insts, const int* active, int n,

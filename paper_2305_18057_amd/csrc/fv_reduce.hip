@@ -155,8 +155,9 @@ __device__ __forceinline__ void norms_from_sums(int nv, long long ncells, const 
   comb = sqrt(cs);
 }
 
+// host: the record goes there too (one instance), or null
 __global__ __launch_bounds__(kRedThreads) void k_finalize(DevInstance* insts, const int* active,
-                                                         int n, const int* n_dev) {
+                                                         int n, const int* n_dev, DevInstance* host) {
   // with a device-resident count the grid is sized for the capacity and the
   // workgroups beyond the live count leave at once (graphs stay valid)
   if (n_dev && (int)blockIdx.x >= *n_dev) return;
@@ -174,61 +175,69 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize(DevInstance* insts, co
   double t = I.t, dt = I.dt, norm_first = I.norm_first;
   long long steps = I.steps;
   int flags = I.flags, have_first = I.have_first, last_step = I.last_step;
-  if (stopped0) return;
+  if (stopped0) {  // (the same for the whole workgroup)
+    if (host) publish(&I, host);
+    return;
+  }
   RedOut R;
   reduce_parts(nt, part, true, true, R);
-  if (threadIdx.x != 0) return;
-  double comb, nrm[5];
-  norms_from_sums(nv, ncells, qref, R.s, nrm, comb);
-  if (!have_first) {
-    norm_first = comb;
-    have_first = 1;
-  }
-  const double drop = norm_first > 0.0 ? comb / norm_first : 0.0;
-  t = last_step ? t_end : t + dt;
-  const double dt_last = dt;
-  steps += 1;
-  int stopped = 0;
-  if (R.bad) {
-    flags |= FLAG_NONPHYS;
-    stopped = 1;
-  }
-  if (drop_tol > 0.0 && drop <= drop_tol) {
-    flags |= FLAG_CONVERGED;
-    stopped = 1;
-  }
-  if (steps >= step_limit) {
-    flags |= FLAG_STEPLIMIT;
-    stopped = 1;
-  }
-  // next time step (the rule of next_dt)
-  if (!stopped) {
-    dt = dt_fixed > 0.0 ? dt_fixed : cfl * R.mn;
-    last_step = 0;
-    if (t_end > 0.0) {
-      if (t >= t_end) {
-        stopped = 1;
-        flags |= FLAG_TEND;
-      } else if (dt >= t_end - t) {
-        dt = t_end - t;
-        last_step = 1;
+  if (threadIdx.x == 0) {
+    double comb, nrm[5];
+    norms_from_sums(nv, ncells, qref, R.s, nrm, comb);
+    if (!have_first) {
+      norm_first = comb;
+      have_first = 1;
+    }
+    const double drop = norm_first > 0.0 ? comb / norm_first : 0.0;
+    t = last_step ? t_end : t + dt;
+    const double dt_last = dt;
+    steps += 1;
+    int stopped = 0;
+    if (R.bad) {
+      flags |= FLAG_NONPHYS;
+      stopped = 1;
+    }
+    if (drop_tol > 0.0 && drop <= drop_tol) {
+      flags |= FLAG_CONVERGED;
+      stopped = 1;
+    }
+    if (steps >= step_limit) {
+      flags |= FLAG_STEPLIMIT;
+      stopped = 1;
+    }
+    // next time step (the rule of next_dt)
+    if (!stopped) {
+      dt = dt_fixed > 0.0 ? dt_fixed : cfl * R.mn;
+      last_step = 0;
+      if (t_end > 0.0) {
+        if (t >= t_end) {
+          stopped = 1;
+          flags |= FLAG_TEND;
+        } else if (dt >= t_end - t) {
+          dt = t_end - t;
+          last_step = 1;
+        }
       }
     }
-  }
 #pragma unroll
-  for (int v = 0; v < 5; ++v) I.norms[v] = nrm[v];
-  I.norm = comb;
-  I.norm_first = norm_first;
-  I.have_first = have_first;
-  I.drop = drop;
-  I.t = t;
-  I.dt_last = dt_last;
-  I.steps = steps;
-  I.raw_min = R.mn;
-  I.flags = flags;
-  I.stopped = stopped;
-  I.dt = dt;
-  I.last_step = last_step;
+    for (int v = 0; v < 5; ++v) I.norms[v] = nrm[v];
+    I.norm = comb;
+    I.norm_first = norm_first;
+    I.have_first = have_first;
+    I.drop = drop;
+    I.t = t;
+    I.dt_last = dt_last;
+    I.steps = steps;
+    I.raw_min = R.mn;
+    I.flags = flags;
+    I.stopped = stopped;
+    I.dt = dt;
+    I.last_step = last_step;
+  }
+  if (host) {
+    __syncthreads();
+    publish(&I, host);
+  }
 }
 
 // host: the record goes there too (one instance), or null
@@ -302,9 +311,9 @@ hipError_t launch_prepare(hipStream_t s, DevInstance* insts, const int* active, 
   return hipGetLastError();
 }
 hipError_t launch_finalize(hipStream_t s, DevInstance* insts, const int* active, int n,
-                           const int* n_dev) {
+                           const int* n_dev, DevInstance* host) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(kRedThreads), 0, s, insts, active, n, n_dev);
+  hipLaunchKernelGGL(k_finalize, dim3(n), dim3(kRedThreads), 0, s, insts, active, n, n_dev, host);
   return hipGetLastError();
 }
 hipError_t launch_put(hipStream_t s, DevInstance* inst, const DevInstance& v, bool whole, bool prep) {
