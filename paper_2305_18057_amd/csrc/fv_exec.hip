@@ -86,7 +86,7 @@ int enqueue_cfl(const StepPlan& P, hipStream_t st) {
     if (s.ntiles <= 0) continue;
     hipError_t e;
     if (s.kind == kSet2D || s.kind == kSet2DNS)
-      e = fvk::launch_cfl2d(std::max(1, std::min((s.ntiles + 3) / 4, 4096)), 256, st, s.tiles,
+      e = fvk::launch_cfl2d(std::max(1, std::min(s.ntiles, 8192)), 256, st, s.tiles,
                             s.ntiles_dev, P.blocks, P.insts);
     else
       e = fvk::launch_cfl3d(std::max(1, std::min(s.ntiles, 8192)), 256, st, s.tiles, s.ntiles_dev,

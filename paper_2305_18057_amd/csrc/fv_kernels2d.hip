@@ -655,19 +655,21 @@ __global__ __launch_bounds__(256) void k_cfl2d(const DevTile* __restrict__ tiles
                                                const int* __restrict__ ntiles_p,
                                                const DevBlock* __restrict__ blocks,
                                                DevInstance* __restrict__ insts) {
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ double s_m[kWavesPerWG];
+  __shared__ int s_b[kWavesPerWG];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int ntiles = *ntiles_p;
-  for (int t = blockIdx.x * kWavesPerWG + wid; t < ntiles; t += gridDim.x * kWavesPerWG) {
+  for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const DevTile tl = tiles[t];
     DevInstance& I = insts[tl.inst];
     const DevBlock& B = blocks[tl.blk];
     double dmin = INFINITY;
     int bad = 0;
-    // the tile's cells in rows, whatever its width (the Navier-Stokes
-    // kernel's tiles are narrow: one column per lane took 28 us for 524,288
-    // cells in tiles of 15 columns)
-    for (int x = lane; x < tl.ncol * tl.n; x += 64) {
+    // a workgroup per tile, its threads over the tile's cells whatever its
+    // width: a tall or narrow tile marched by one wavefront is a chain of
+    // loads (4.2 M cells in tiles of 32 rows 54 us, 524,288 in tiles of 15
+    // columns 28 us)
+    for (int x = threadIdx.x; x < tl.ncol * tl.n; x += 64 * kWavesPerWG) {
       const int r = x / tl.ncol, i = tl.i0 + x - r * tl.ncol;
       const int j = tl.j0 + r;
       const long long idx = (long long)j * B.ni + i;
@@ -701,11 +703,17 @@ __global__ __launch_bounds__(256) void k_cfl2d(const DevTile* __restrict__ tiles
     const double m = wave_min(dmin);
     const int b = wave_or(bad);
     if (lane == 0) {
+      s_m[w] = m;
+      s_b[w] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
       double* part = I.part + tl.local;
       const long long ps = I.ntiles;
-      part[5 * ps] = m;
-      part[6 * ps] = (double)b;
+      part[5 * ps] = fmin(fmin(s_m[0], s_m[1]), fmin(s_m[2], s_m[3]));
+      part[6 * ps] = (double)(s_b[0] | s_b[1] | s_b[2] | s_b[3]);
     }
+    __syncthreads();
   }
 }
 
