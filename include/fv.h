@@ -283,7 +283,7 @@ typedef struct fv_grid_stats {
   long long cells;        /* interior cells */
   long long tiles;        /* work-list entries */
   int tile_rows;          /* 2D: rows per tile; 3D: planes per tile */
-  int tile_cols;          /* cells per tile row (i) */
+  int tile_cols;          /* cells per row (i) of the first tile */
   int tile_ny;            /* 3D: j-rows per tile (1 in 2D) */
   int launch_blocks;      /* persistent workgroups per stage launch */
   size_t workspace_bytes;

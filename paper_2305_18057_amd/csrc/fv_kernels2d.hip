@@ -667,8 +667,8 @@ __global__ __launch_bounds__(256) void k_cfl2d(const DevTile* __restrict__ tiles
     int bad = 0;
     // a workgroup per tile, its threads over the tile's cells whatever its
     // width: a tall or narrow tile marched by one wavefront is a chain of
-    // loads (4.2 M cells in tiles of 32 rows 54 us, 524,288 in tiles of 15
-    // columns 28 us)
+    // loads (4.2 M cells in tiles of 32 rows 54 us, now 42; 524,288 in tiles
+    // of 15 columns 28 us, now 12)
     for (int x = threadIdx.x; x < tl.ncol * tl.n; x += 64 * kWavesPerWG) {
       const int r = x / tl.ncol, i = tl.i0 + x - r * tl.ncol;
       const int j = tl.j0 + r;
