@@ -956,60 +956,4 @@ __host__ __device__ __forceinline__ double cell_dt_limit_visc(const double* q, c
   return vol / lam;
 }
 
-// The same limit from the refined hardware estimates, for the last stage of the
-// FP64 kernels: IEEE division and square root take about ten and twenty
-// instructions each, five to seven of them per cell (a last stage of the
-// 524,288-cell inlet 24.1 us against 21.3 us of a middle one).  Results are
-// within an ulp of the form above.  rho and p finite and positive imply that
-// every component is finite: an infinite or NaN momentum makes p -inf or NaN,
-// an infinite energy p infinite.  mu > 0 adds the viscous term of
-// cell_dt_limit_visc.
-template <int ND>
-__device__ __forceinline__ double cell_dt_limit_fast(const double* q, const double (*Sb)[3], double vol,
-                                                     double gamma, double mu, double prandtl, int& bad) {
-  constexpr int E = ND + 1;
-  typedef M<double> R;
-  const double rho = q[0], ir = R::rcp(rho);
-  double m2 = q[1] * q[1];
-#pragma unroll
-  for (int a = 1; a < ND; ++a) m2 = fmad(q[1 + a], q[1 + a], m2);
-  const double p = (gamma - 1.0) * fmad(-0.5 * ir, m2, q[E]);
-  if (!(rho > 0.0 && p > 0.0 && rho < INFINITY && p < INFINITY)) {
-    bad = 1;
-    return INFINITY;
-  }
-  const double c = R::root(gamma * p * ir);
-  double lam = 0.0, ss = 0.0;
-#pragma unroll
-  for (int d = 0; d < ND; ++d) {
-    double ms = q[1] * Sb[d][0], s2 = Sb[d][0] * Sb[d][0];
-#pragma unroll
-    for (int a = 1; a < ND; ++a) {
-      ms = fmad(q[1 + a], Sb[d][a], ms);
-      s2 = fmad(Sb[d][a], Sb[d][a], s2);
-    }
-    lam += fmad(c, R::root(s2), fabs(ms * ir));
-    ss += s2;
-  }
-  if (mu > 0.0) lam = fmad(2.0 * fmax(4.0 / 3.0, gamma / prandtl) * (mu * ir), ss * R::rcp(vol), lam);
-  // vol / lam, the quotient corrected by its remainder
-  const double il = R::rcp(lam), dt = vol * il;
-  return fmad(fmad(-lam, dt, vol), il, dt);
-}
-
-// the limit of the last stage of a kernel whose flux runs in T: FP32-flux keeps
-// the IEEE form, whose time steps its results are compared by
-template <int ND, typename T>
-__device__ __forceinline__ double stage_dt_limit(const double* q, const double (*Sb)[3], double vol,
-                                                 double gamma, double mu, double prandtl, int& bad) {
-  if constexpr (sizeof(T) == 8) {
-    return cell_dt_limit_fast<ND>(q, Sb, vol, gamma, mu, prandtl, bad);
-  } else {
-    if constexpr (ND == 2) {
-      if (mu > 0.0) return cell_dt_limit_visc(q, Sb, vol, gamma, mu, prandtl, bad);
-    }
-    return cell_dt_limit<ND>(q, Sb, vol, gamma, bad);
-  }
-}
-
 }  // namespace fvk

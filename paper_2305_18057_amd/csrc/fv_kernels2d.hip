@@ -536,7 +536,7 @@ __device__ __forceinline__ void tile2d(const DevTile& tl, const DevBlock* __rest
               Sb[1][1] = areaJ;
             }
             Sb[0][2] = Sb[1][2] = 0.0;
-            dmin = fmin(dmin, stage_dt_limit<2, T>(out, Sb, vol, gamma, 0.0, 0.0, bad));
+            dmin = fmin(dmin, cell_dt_limit<2>(out, Sb, vol, gamma, bad));
           }
         }
       }

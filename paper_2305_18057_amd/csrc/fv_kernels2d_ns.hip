@@ -591,7 +591,8 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
           }
         }
         if constexpr (SK::cfl)
-          dmin = fmin(dmin, stage_dt_limit<2, T>(out, Sb, vol, gamma, mu, I.prandtl, bad));
+          dmin = fmin(dmin, mu > 0.0 ? cell_dt_limit_visc(out, Sb, vol, gamma, mu, I.prandtl, bad)
+                                     : cell_dt_limit<2>(out, Sb, vol, gamma, bad));
       }
     }
   }

@@ -479,7 +479,7 @@ __device__ void tile3d(const DevTile& tl, const DevBlock* __restrict__ blocks, D
           if constexpr (SK::cfl) {
             const double Sb[3][3] = {{B.area[0], 0.0, 0.0}, {0.0, B.area[1], 0.0},
                                      {0.0, 0.0, B.area[2]}};
-            dmin = fmin(dmin, stage_dt_limit<3, T>(out, Sb, vol, gamma, 0.0, 0.0, bad));
+            dmin = fmin(dmin, cell_dt_limit<3>(out, Sb, vol, gamma, bad));
           }
         }
       }

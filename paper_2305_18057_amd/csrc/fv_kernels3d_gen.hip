@@ -432,7 +432,7 @@ __device__ void tile_gen(const DevTile& tl, const DevBlock* __restrict__ blocks,
             Sb[1][x] = 0.5 * (L.s[1][x][g] + L.s[1][x][g + nc]);
             Sb[2][x] = 0.5 * (sk[x] + So[x]);
           }
-          dmin = fmin(dmin, stage_dt_limit<3, T>(out, Sb, vol, gamma, 0.0, 0.0, bad));
+          dmin = fmin(dmin, cell_dt_limit<3>(out, Sb, vol, gamma, bad));
         }
       }
 #pragma unroll
