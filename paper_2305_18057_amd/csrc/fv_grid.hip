@@ -207,14 +207,14 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
   g->hinst.step_limit = 0;
   g->hinst.stopped = 1;
   g->hinst.flags = fvk::FLAG_NONPHYS;  // no state yet
-  // tile shape: autotune table for this size class, else the default
-  const char* tp = tune_path(nullptr);
-  TileShape tsh;
-  if (tune_lookup(tp, tune_key(g->hg, FV_FP64), tsh)) {
-    g->shape[0] = g->shape[1] = tsh;
-  } else {
-    g->shape[0] = default_shape(g->hg, g->hg.ndim == 2 && !g->hg.two_lists());
-    g->shape[1] = default_shape(g->hg, g->hg.ndim == 2);
+  // tile shapes: the autotune table's for this size class, else the default; each
+  // list under the key of the kernel that runs it (a shape of the other kernel
+  // fits badly: slabs as low as the Euler kernel's rows leave most of a
+  // Navier-Stokes workgroup's threads without a cell)
+  for (int x = 0; x < 2; ++x) {
+    const bool ns = g->hg.ndim == 2 && (x == 1 || !g->hg.two_lists());
+    if (!tune_lookup(tune_path(nullptr), tune_key(g->hg, FV_FP64, ns), g->shape[x]))
+      g->shape[x] = default_shape(g->hg, ns);
   }
   g->plan.ns = g->hg.ndim == 2 && !g->hg.two_lists();
   st = fvgrid::upload_tiles(g);
