@@ -60,8 +60,8 @@ struct NsLds {
   double w[3][kNsW];            // u, v, p/rho of the slab and one ring
   double nx[kNsN], ny[kNsN];    // nodes of the slab and one ring
   double f[2][4][kNsThreads];   // i- and j-face fluxes (times area, minus viscous)
-  double g[2][kNsThreads];      // x, y of the centres of the ghosts beyond i-min and
-                                // i-max (H each), j-min and j-max (W each)
+  double g[2][kNsThreads];      // x, y differences of the centres at the block's faces
+                                // i-min and i-max (H each), j-min and j-max (W each)
   double red[4][8];             // per-wave partials
 };
 
@@ -189,58 +189,53 @@ __device__ void ns_cell(const DevBlock* __restrict__ blocks, const DevBlock* Bp,
   }
 }
 
-// Centre of cell (i, j) of B, inside or one ghost layer outside one face
-__device__ void ns_centre(const DevBlock* __restrict__ blocks, const DevBlock& B, int i, int j,
-                          double& cx, double& cy) {
-  const bool iin = i >= 0 && i < B.ni, jin = j >= 0 && j < B.nj;
-  if (iin && jin) {
-    centre_of(B, i, j, cx, cy);
-    return;
-  }
-  if (!iin && !jin) {  // corner: never a face's neighbour
-    cx = cy = 0.0;
-    return;
-  }
-  const int d = iin ? 1 : 0;
-  const int side = (d == 0 ? i : j) < 0 ? 0 : 1;
-  const int f = 2 * d + side;
-  const int n = d == 0 ? B.ni : B.nj;
-  // midpoint of the boundary face
-  double x0, y0, x1, y1;
-  const int w = side == 0 ? 0 : n;
-  if (d == 0) {
-    node_of(B, w, j, x0, y0);
-    node_of(B, w, j + 1, x1, y1);
-  } else {
-    node_of(B, i, w, x0, y0);
-    node_of(B, i + 1, w, x1, y1);
-  }
-  const double mx = 0.5 * (x0 + x1), my = 0.5 * (y0 + y1);
-  const int kind = B.bc_kind[f];
+// Difference of the centres of the two cells at face t of side f of B, from the
+// low to the high side.  Through a link it is formed as inside a block, a
+// quarter of the difference of the two cells' nodes beyond the face, plus that
+// of the two blocks' nodes on the face (0 where they agree): both blocks get
+// the face's difference in one form, bit for bit that of the uncut grid.  At
+// other faces the ghost's centre is the image moved by the offset of the
+// periodic faces, or the own centre reflected through the face's midpoint.
+__device__ void ns_dcentre(const DevBlock* __restrict__ blocks, const DevBlock& B, int f, int t,
+                           double& dx, double& dy) {
+  const int d = f >> 1, side = f & 1;
+  const int n = d == 0 ? B.ni : B.nj, kind = B.bc_kind[f];
+  auto pair = [&](const DevBlock& S, int l, double& px, double& py) {  // line l of nodes across d
+    double x0, y0, x1, y1;
+    node_of(S, d == 0 ? l : t, d == 0 ? t : l, x0, y0);
+    node_of(S, d == 0 ? l : t + 1, d == 0 ? t + 1 : l, x1, y1);
+    px = x0 + x1;
+    py = y0 + y1;
+  };
+  double fx, fy;
+  pair(B, side == 0 ? 0 : n, fx, fy);
   if (kind == BC_BLOCK) {
     const DevBlock& N = blocks[B.bc_nbr[f]];
-    const int along = side == 0 ? (d == 0 ? N.ni : N.nj) - 1 : 0;
-    centre_of(N, d == 0 ? along : i, d == 0 ? j : along, cx, cy);
-  } else if (kind == BC_PERIODIC) {
-    const int along = side == 0 ? n - 1 : 0;
-    const int wo = side == 0 ? n : 0;
-    if (d == 0) {
-      node_of(B, wo, j, x0, y0);
-      node_of(B, wo, j + 1, x1, y1);
-    } else {
-      node_of(B, i, wo, x0, y0);
-      node_of(B, i + 1, wo, x1, y1);
-    }
-    const double ox = 0.5 * (x0 + x1), oy = 0.5 * (y0 + y1);
-    centre_of(B, d == 0 ? along : i, d == 0 ? j : along, cx, cy);
-    cx += mx - ox;
-    cy += my - oy;
-  } else {
-    const int along = side == 0 ? 0 : n - 1;
-    centre_of(B, d == 0 ? along : i, d == 0 ? j : along, cx, cy);
-    cx = 2.0 * mx - cx;
-    cy = 2.0 * my - cy;
+    const int m = d == 0 ? N.ni : N.nj;
+    double ix, iy, gx, gy, ox, oy;
+    pair(B, side == 0 ? 1 : n - 1, ix, iy);
+    pair(N, side == 0 ? m : 0, gx, gy);
+    pair(N, side == 0 ? m - 1 : 1, ox, oy);
+    dx = 0.25 * (side == 0 ? (ix - ox) + (fx - gx) : (ox - ix) + (gx - fx));
+    dy = 0.25 * (side == 0 ? (iy - oy) + (fy - gy) : (oy - iy) + (gy - fy));
+    return;
   }
+  const int in = side == 0 ? 0 : n - 1;
+  double cx, cy, gx, gy;
+  centre_of(B, d == 0 ? in : t, d == 0 ? t : in, cx, cy);
+  if (kind == BC_PERIODIC) {
+    const int out = n - 1 - in;
+    double ox, oy;
+    pair(B, side == 0 ? n : 0, ox, oy);
+    centre_of(B, d == 0 ? out : t, d == 0 ? t : out, gx, gy);
+    gx += 0.5 * fx - 0.5 * ox;
+    gy += 0.5 * fy - 0.5 * oy;
+  } else {
+    gx = fx - cx;  // twice the midpoint
+    gy = fy - cy;
+  }
+  dx = side == 0 ? cx - gx : gx - cx;
+  dy = side == 0 ? cy - gy : gy - cy;
 }
 
 // The rule of one face of B and the block its ghosts are copied from, read
@@ -395,17 +390,16 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
       if (nn[h] >= 0)
         node_of(B, min(max(i0 - 1 + x - r * np, 0), ni), min(max(js - 1 + r, 0), nj), xs[h], ys[h]);
     }
-    // centres of the ghosts beyond the block's faces (boundary tiles only)
+    // differences of the centres at the block's faces (boundary tiles only)
     if (mu > 0.0 && !inside && tid < 2 * (nr + nc)) {
       const bool di = tid < 2 * nr;
       const int y = di ? tid : tid - 2 * nr, n = di ? nr : nc;
       const int side = y >= n ? 1 : 0, t = y - side * n;
       if (di ? (side == 0 ? lo_edge : hi_edge) : (side == 0 ? js == 0 : js + nr == nj)) {
-        double cx, cy;
-        ns_centre(blocks, B, di ? (side == 0 ? -1 : ni) : i0 + t, di ? js + t : (side == 0 ? -1 : nj), cx,
-                  cy);
-        L.g[0][tid] = cx;
-        L.g[1][tid] = cy;
+        double gx, gy;
+        ns_dcentre(blocks, B, (di ? 0 : 2) + side, (di ? js : i0) + t, gx, gy);
+        L.g[0][tid] = gx;
+        L.g[1][tid] = gy;
       }
     }
 #pragma unroll
@@ -505,15 +499,9 @@ __device__ void tile_ns(const DevTile& tl, const DevBlock* __restrict__ blocks, 
         double dy = 0.25 * ((Y[n] + Y[t + n]) - (Y[-n] + Y[t - n]));
         const bool lo = di ? lo_edge && fc == 0 : js + fr == 0;
         if (lo || (di ? hi_edge && fc == nc : js + fr == nj)) {
-          // the ghost's centre and the inside cell's (half the sums of its
-          // two nodes on the face and two beyond)
-          const int m = lo ? n : -n;
-          const double cx = 0.25 * ((X[0] + X[t]) + (X[m] + X[t + m]));
-          const double cy = 0.25 * ((Y[0] + Y[t]) + (Y[m] + Y[t + m]));
           const int y = di ? (lo ? 0 : nr) + fr : 2 * nr + (lo ? 0 : nc) + fc;
-          const double gx = L.g[0][y], gy = L.g[1][y];
-          dx = lo ? cx - gx : gx - cx;
-          dy = lo ? cy - gy : gy - cy;
+          dx = L.g[0][y];
+          dy = L.g[1][y];
         }
         T Fv[4];
         visc_flux<T>(wL, wR, wt, dx, dy, Sx, Sy, tmu, kq, Fv);
