@@ -213,8 +213,7 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
   // Navier-Stokes workgroup's threads without a cell)
   for (int x = 0; x < 2; ++x) {
     const bool ns = g->hg.ndim == 2 && (x == 1 || !g->hg.two_lists());
-    if (!tune_lookup(tune_path(nullptr), tune_key(g->hg, FV_FP64, ns), g->shape[x]))
-      g->shape[x] = default_shape(g->hg, ns);
+    g->shape[x] = grid_shape(g->hg, ns, tune_path(nullptr), FV_FP64);
   }
   g->plan.ns = g->hg.ndim == 2 && !g->hg.two_lists();
   st = fvgrid::upload_tiles(g);
@@ -466,6 +465,7 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
     // as is; the state is untouched, only the per-tile minima are redone
     TileShape rec;
     if (tune_lookup(tune_path(cache_path), tune_key(g->hg, p->precision, tns), rec)) {
+      rec = grid_shape(g->hg, tns, tune_path(cache_path), p->precision);
       if (rec.rows != shape.rows || rec.ny != shape.ny) {
         shape = rec;
         if ((st = upload_tiles(g))) return st;
@@ -504,6 +504,7 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
   }
   // and the shape an untuned grid gets, where it is none of these
   const TileShape def = default_shape(g->hg, tns);
+  const size_t listed = cands.size();
   if (std::none_of(cands.begin(), cands.end(),
                    [&](const TileShape& c) { return c.rows == def.rows && c.ny == def.ny; }))
     cands.push_back(def);
@@ -579,12 +580,15 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
     st = time_shape(cands[order[r]], again);
     ms[order[r]] = std::min(ms[order[r]], again);
   }
-  TileShape best = shape;
+  TileShape best = shape, entry = shape;
   double best_ms = 1e30;
   for (size_t c = 0; c < cands.size(); ++c)
     if (ms[c] < best_ms) {
       best_ms = ms[c];
-      best = cands[c];
+      best = entry = cands[c];
+      // the default is fitted to this grid's extents: the table, which every
+      // grid of the size class reads, says "the default", not its numbers
+      if (c >= listed) entry = TileShape{0, 0};
     }
   if (st) return st;
   shape = best;
@@ -601,6 +605,6 @@ extern "C" int fv_tune(fv_grid* g, const fv_params* p, const char* cache_path) {
   if (st) return st;
   g->hinst.steps = keep.steps;
   g->hinst.t = keep.t;
-  tune_store(tune_path(cache_path), tune_key(g->hg, p->precision, tns), best, best_ms);
+  tune_store(tune_path(cache_path), tune_key(g->hg, p->precision, tns), entry, best_ms);
   return FV_OK;
 }

@@ -92,11 +92,7 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
   if (st) return st;
   hipStream_t s = (hipStream_t)hip_stream;
 
-  TileShape sh = default_shape(hg, ns);
-  {
-    TileShape tsh;
-    if (tune_lookup(tune_path(nullptr), tune_key(hg, p->precision, ns), tsh)) sh = tsh;
-  }
+  TileShape sh = grid_shape(hg, ns, tune_path(nullptr), p->precision);
   std::vector<fvk::DevTile> htiles;
   build_tiles(hg, sh, 0, 0, htiles, ns);
   // the list of low tiles can be longer than reserved above: taller ones where

@@ -90,11 +90,15 @@ void gen_tile_shape(int ni, int nj, int& w, int& h);
 void ns_tile_shape(int ni, int n, int& w, int& h);
 int size_class(const HostGrid& g);
 
-// autotune table (JSON file of "key": {"rows": r, "ny": y})
+// autotune table (JSON file of "key": {"rows": r, "ny": y}; 0 rows: the default
+// shape of each grid of the class)
 std::string tune_key(const HostGrid& g, int precision, bool ns = false);
 bool tune_lookup(const char* path, const std::string& key, TileShape& sh);
 void tune_store(const char* path, const std::string& key, const TileShape& sh, double ms);
 const char* tune_path(const char* given);
+// the shape of a grid of its own: the table's, else (or where the table says so)
+// its default
+TileShape grid_shape(const HostGrid& g, bool ns, const char* path, int precision);
 
 void params_to_inst(const fv_params* p, double gamma, fvk::DevInstance& I);
 int check_params(const fv_params* p);

@@ -643,6 +643,12 @@ void tune_store(const char* path, const std::string& key, const TileShape& sh, d
   rename(tmp.c_str(), path);
 }
 
+TileShape grid_shape(const HostGrid& g, bool ns, const char* path, int precision) {
+  TileShape sh;
+  if (tune_lookup(path, tune_key(g, precision, ns), sh) && sh.rows > 0) return sh;
+  return default_shape(g, ns);
+}
+
 int rk_of(const fv_params* p) { return p->rk == 0 ? 3 : p->rk; }
 
 int check_params(const fv_params* p) {

@@ -574,7 +574,7 @@ int submit(fv_server* S, const fv_grid_desc* desc, const double* U0, const doubl
   TileShape sh = default_shape(r->hg, ns, true);
   TileShape tsh;
   if (tune_lookup(tune_path(S->tune_path.empty() ? nullptr : S->tune_path.c_str()),
-                  tune_key(r->hg, S->d.precision, ns), tsh)) {
+                  tune_key(r->hg, S->d.precision, ns), tsh) && tsh.rows > 0) {
     // A grid alone is tuned to fill the device: down to single rows or planes,
     // or up to tiles whose rounds come out even.  In a batch the other
     // instances fill it; the lowest tiles only do more work per cell (64
