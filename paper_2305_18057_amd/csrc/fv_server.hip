@@ -580,12 +580,13 @@ int submit(fv_server* S, const fv_grid_desc* desc, const double* U0, const doubl
     // instances fill it; the lowest tiles only do more work per cell (64
     // FP32-flux instances, 5.7 M cells: 4.38 G cell-updates/s with 1-row tiles
     // for the smallest, 4.7 to 4.8 without), and 36 or 59 planes of a 3D box make
-    // the tail of every stage (256 requests in FP64 5.34 G, at most 20 planes
-    // 6.10; in FP32-flux 6.08 and 7.63).
+    // the tail of every stage (256 requests in FP64 5.34 G, at most the 20 planes
+    // of an untuned box 6.10; in FP32-flux 6.08 and 7.63).
+    const int most = sh.rows;
     sh = tsh;
     if (r->hg.ndim == 2) sh.rows = std::max(sh.rows, 2);
     else if (r->hg.gen3) sh.rows = std::max(sh.rows, 4);
-    else sh.rows = std::min(std::max(sh.rows, 8), 20);
+    else sh.rows = std::min(std::max(sh.rows, 8), most);
   }
   r->shape = sh;
   r->kind = kind_of(r->hg, sh, ns);
