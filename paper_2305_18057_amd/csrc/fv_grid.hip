@@ -3,12 +3,54 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 
 #include "fv_grid_impl.h"
 
 using namespace fvrt;
 
+fv_grid::~fv_grid() {
+  if (pin) fvgrid::give_record(pin);
+}
+
 namespace fvgrid {
+
+namespace {
+constexpr int kSlabRecords = 64;
+constexpr size_t kRecordStride = (sizeof(fvk::DevInstance) + 63) / 64 * 64;  // no line shared
+std::mutex g_rec_mu;
+void* g_rec_free = nullptr;  // records not in use, linked through their first word
+}  // namespace
+
+fvk::DevInstance* take_record() {
+  std::lock_guard<std::mutex> lk(g_rec_mu);
+  if (!g_rec_free) {
+    char* slab = nullptr;
+    // portable: handles of every device draw on it
+    if (hipHostMalloc((void**)&slab, kRecordStride * kSlabRecords, hipHostMallocPortable) != hipSuccess)
+      return nullptr;
+    for (int k = 0; k < kSlabRecords; ++k) {
+      void* r = slab + k * kRecordStride;
+      *(void**)r = g_rec_free;
+      g_rec_free = r;
+    }
+  }
+  void* r = g_rec_free;
+  g_rec_free = *(void**)r;
+  return (fvk::DevInstance*)r;
+}
+
+void give_record(fvk::DevInstance* r) {
+  std::lock_guard<std::mutex> lk(g_rec_mu);
+  *(void**)r = g_rec_free;
+  g_rec_free = r;
+}
+
+// the record as a launch's argument; wait_inst follows
+static fvk::DevInstance* pin_out(fv_grid* g) {
+  g->pin_busy = true;
+  return g->pin;
+}
 
 // the tile list of the Navier-Stokes (ns) or the Euler kernel for the coming
 // launches.  The instance's tile count sizes its partials (value-major) and
@@ -65,12 +107,13 @@ int put_inst(fv_grid* g) {
 // the record the kernels have left in pinned memory, once they are done
 static int wait_inst(fv_grid* g) {
   FV_HIP(hipStreamSynchronize(g->stream));
+  g->pin_busy = false;
   g->hinst = *g->pin;
   return FV_OK;
 }
 
 int get_inst(fv_grid* g) {
-  FV_HIP(fvk::launch_publish(g->stream, g->d_inst, g->pin));
+  FV_HIP(fvk::launch_publish(g->stream, g->d_inst, pin_out(g)));
   return wait_inst(g);
 }
 
@@ -89,7 +132,7 @@ void fill_info(const fv_grid* g, fv_step_info* info) {
 int cfl_pass(fv_grid* g) {
   const int err = fvexec::enqueue_cfl(g->plan, g->stream);
   if (err) return err;
-  FV_HIP(fvk::launch_cfl_init(g->stream, g->d_inst, nullptr, 1, g->pin));
+  FV_HIP(fvk::launch_cfl_init(g->stream, g->d_inst, nullptr, 1, pin_out(g)));
   g->cfl_mu = g->hinst.mu;
   g->cfl_pr = g->hinst.prandtl;
   return wait_inst(g);
@@ -175,10 +218,8 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
     delete g;
     return e;
   };
-  if (hipHostMalloc((void**)&g->pin, sizeof(fvk::DevInstance), hipHostMallocDefault) != hipSuccess) {
-    g->pin = nullptr;
-    return fail(set_error(FV_E_NOMEM, "pinned host allocation failed"));
-  }
+  g->pin = take_record();
+  if (!g->pin) return fail(set_error(FV_E_NOMEM, "pinned host allocation failed"));
   hipError_t he = hipMemcpyAsync(g->d_blocks, g->hblocks.data(),
                                  sizeof(fvk::DevBlock) * g->hblocks.size(), hipMemcpyHostToDevice,
                                  g->stream);
@@ -229,7 +270,8 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
 
 extern "C" int fv_destroy_grid(fv_grid* g) {
   if (!g) return FV_E_INVAL;
-  if (g->stream) (void)hipStreamSynchronize(g->stream);
+  // (the record goes to another handle: nothing may still write it)
+  if (g->stream || g->pin_busy) (void)hipStreamSynchronize(g->stream);
   g->graphs.clear();
   delete g;
   return FV_OK;
@@ -292,7 +334,7 @@ extern "C" int fv_residual(fv_grid* g, const fv_params* p, double* R, int on_dev
   g->plan.lim = p->limiter;
   st = fvexec::enqueue_stage(g->plan, 0, p->precision == FV_FP32_FLUX, dst, g->stream);
   if (st) return st;
-  FV_HIP(fvk::launch_rnorms(g->stream, g->d_inst, nullptr, 1, g->pin));
+  FV_HIP(fvk::launch_rnorms(g->stream, g->d_inst, nullptr, 1, pin_out(g)));
   if (R && !on_device)
     FV_HIP(hipMemcpyAsync(R, g->d_u[1], sizeof(double) * g->hg.state_size, hipMemcpyDeviceToHost,
                           g->stream));
@@ -343,7 +385,8 @@ static int run_steps(fv_grid* g, const fv_params* p, long long nsteps, double dr
   const bool check = drop_tol > 0.0;
   while (left > 0) {
     const int c = (int)std::min<long long>(left, chunk);
-    st = fvexec::enqueue_steps(g->plan, fp32, c, g->stream, &g->graphs, 0, left == c ? g->pin : nullptr);
+    st = fvexec::enqueue_steps(g->plan, fp32, c, g->stream, &g->graphs, 0,
+                               left == c ? pin_out(g) : nullptr);
     if (st) return st;
     left -= c;
     since_check += c;

@@ -23,6 +23,7 @@ struct fv_grid {
   std::vector<fvk::DevTile> htiles[2];
   fvk::DevInstance hinst;
   fvk::DevInstance* pin = nullptr;  // pinned: where the kernels leave the record of a call
+  bool pin_busy = false;  // kernels that write it may still run (a call failed half-way)
   fvrt::TileShape shape[2];
   int list = 0;  // the list in use
   fvexec::StepPlan plan;
@@ -32,12 +33,18 @@ struct fv_grid {
   // viscosity with which the device's time-step bound of the current state
   // was formed (the viscous term enters it)
   double cfl_mu = 0.0, cfl_pr = 0.0;
-  ~fv_grid() {
-    if (pin) (void)hipHostFree(pin);
-  }
+  ~fv_grid();
 };
 
 namespace fvgrid {
+
+// Pinned records, one per handle, from slabs that are kept until the process
+// ends: freeing pinned memory waits for the whole device, and allocating it
+// takes 26 us (a handle of 128 x 64 cells 84 us to make and 23 us to destroy,
+// now 59 and 1).  The slabs hold as many records as there were handles at
+// once, 384 bytes each.  Any thread.
+fvk::DevInstance* take_record();  // nullptr: no pinned memory left
+void give_record(fvk::DevInstance* r);
 
 // a grid over a validated host grid (the descriptor path and the CPU-GPU
 // split's GPU part, whose halo block is read but never computed)
