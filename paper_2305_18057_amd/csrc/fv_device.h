@@ -459,8 +459,8 @@ __host__ __device__ __forceinline__ void roe_flux_plain(const T* __restrict__ qL
 //   - the Roe weights from D = sqrt(rho_R / rho_L): w_L = 1/(1+D), w_R = D w_L,
 //     rho~ = D rho_L (one root and one reciprocal; two roots, their
 //     reciprocals and one more reciprocal above);
-//   - no velocities of the two sides: |m|^2/rho, V_n and the averages come
-//     from the momenta;
+//   - the averages come from the momenta (the kinetic energy as u . m: the
+//     square of a momentum overflows, or vanishes, long before the state does);
 //   - F = Q_L (V_L + |V|) + Q_R (V_R - |V|) + ... per component, with half the
 //     area multiplied into the five coefficients instead of the components;
 //   - Harten's fix without selects: |l| + max(delta - |l|, 0)^2 / (2 delta).
@@ -484,35 +484,35 @@ __host__ __device__ __forceinline__ void roe_flux_f64(const double* __restrict__
   const double wL = R::rcp(1.0 + D);
   const double bL = wL * irL, bR = (wL * D) * irR;
   const double rt = D * qL[0];
-  double mL = qL[1] * qL[1], mR = qR[1] * qR[1];
+  double uL[ND], uR[ND], kL = 0.0, kR = 0.0;  // velocities of the sides, and u . m
 #pragma unroll
-  for (int a = 1; a < ND; ++a) {
-    mL = fmad(qL[1 + a], qL[1 + a], mL);
-    mR = fmad(qR[1 + a], qR[1 + a], mR);
+  for (int a = 0; a < ND; ++a) {
+    uL[a] = qL[1 + a] * irL;
+    uR[a] = qR[1 + a] * irR;
+    kL = a == 0 ? uL[0] * qL[1] : fmad(uL[a], qL[1 + a], kL);
+    kR = a == 0 ? uR[0] * qR[1] : fmad(uR[a], qR[1 + a], kR);
   }
-  const double pL = K.gm1 * fmad(-0.5 * irL, mL, qL[E]);
-  const double pR = K.gm1 * fmad(-0.5 * irR, mR, qR[E]);
+  const double pL = K.gm1 * fmad(-0.5, kL, qL[E]);
+  const double pR = K.gm1 * fmad(-0.5, kR, qR[E]);
   double ut[ND];
 #pragma unroll
   for (int a = 0; a < ND; ++a) ut[a] = fmad(bL, qL[1 + a], bR * qR[1 + a]);
   double VL, VR, V, q2 = ut[0] * ut[0];
   if constexpr (AX >= 0) {
-    VL = qL[1 + AX];
-    VR = qR[1 + AX];
+    VL = uL[AX];
+    VR = uR[AX];
     V = ut[AX];
   } else {
-    VL = qL[1] * n[0];
-    VR = qR[1] * n[0];
+    VL = uL[0] * n[0];
+    VR = uR[0] * n[0];
     V = ut[0] * n[0];
 #pragma unroll
     for (int a = 1; a < ND; ++a) {
-      VL = fmad(qL[1 + a], n[a], VL);
-      VR = fmad(qR[1 + a], n[a], VR);
+      VL = fmad(uL[a], n[a], VL);
+      VR = fmad(uR[a], n[a], VR);
       V = fmad(ut[a], n[a], V);
     }
   }
-  VL *= irL;
-  VR *= irR;
 #pragma unroll
   for (int a = 1; a < ND; ++a) q2 = fmad(ut[a], ut[a], q2);
   const double H = fmad(bL, qL[E] + pL, bR * (qR[E] + pR));
