@@ -344,15 +344,16 @@ int fv_hetero_destroy(fv_hetero* h);
  * with the same kernels, tile shapes and results as fv_create_grid +
  * fv_set_state + fv_step.  Every other buffer (block table, instance record,
  * tile list, reduction partials, node coordinates, the two RK stage buffers)
- * lives in one static device array of FV_NOALLOC_SCRATCH_BYTES per device,
- * held until the process ends; a grid that needs more is rejected with
- * FV_E_NOMEM before any device work (the 4 x 512 x 256 inlet grid needs about
- * 42 MB).  The call calls no hipMalloc/hipFree, launches the kernels one by
- * one (no graph) on hip_stream and returns when info is on the host.  All
- * calls of the process on one device share the array: they are serialized by
- * a lock and each waits for its own work, so they never overlap; work of
- * another call on the same device that reaches the array by other means
- * would race with it.  The info's t, steps and drop count from this call. */
+ * lives in one static device array of FV_NOALLOC_SCRATCH_BYTES (and 2 MiB for
+ * longer tile lists) per device, held until the process ends; a grid that needs
+ * more is rejected with FV_E_NOMEM before any device work (the 4 x 512 x 256
+ * inlet grid needs about 42 MB).  The call calls no hipMalloc/hipFree,
+ * launches the kernels one by one (no graph) on hip_stream and returns when
+ * info is on the host.  All calls of the process on one device share the
+ * array: they are serialized by a lock and each waits for its own work, so
+ * they never overlap; work of another call on the same device that reaches the
+ * array by other means would race with it. The info's t, steps and drop count
+ * from this call. */
 #define FV_NOALLOC_SCRATCH_BYTES (64u << 20)
 size_t fv_noalloc_scratch_bytes(void);
 int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_params* p, int nsteps,

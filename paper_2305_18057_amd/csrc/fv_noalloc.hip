@@ -17,12 +17,17 @@ using namespace fvrt;
 namespace {
 
 constexpr size_t kScratchBytes = (size_t)FV_NOALLOC_SCRATCH_BYTES;
+// Room beyond that limit for a tile list that is longer than the lowest tiles
+// the limit reckons with (64 columns; general 3D tiles split 61 to 64 columns
+// in two).  At 64 planes a tile, over blocks of up to 400 x 100 cells, the
+// excess is at most 1.9% of the rest (61 x 1 x 1 cells, one tile of 104 bytes).
+constexpr size_t kListSlack = 2u << 20;
 constexpr int kMaxDevices = 64;
 
 // One copy per device the library runs on, held until the process ends.  In
 // host code this name only stands in for the symbol: its device address comes
 // from hipGetSymbolAddress, per device, below.
-__device__ __align__(256) unsigned char scratch[kScratchBytes];
+__device__ __align__(256) unsigned char scratch[kScratchBytes + kListSlack];
 
 std::mutex g_mu;  // one call at a time in the process: the array is shared
 char* g_scratch_ptr[kMaxDevices] = {};
@@ -99,7 +104,7 @@ extern "C" int fv_step_noalloc(const fv_grid_desc* desc, double* d_U, const fv_p
   // the scratch has no room for it
   while ((long long)htiles.size() > L.max_tiles) {
     const InstLayout M = noalloc_layout(hg, (long long)htiles.size());
-    if (M.total <= kScratchBytes) {
+    if (M.total <= kScratchBytes + kListSlack) {
       L = M;
       break;
     }
