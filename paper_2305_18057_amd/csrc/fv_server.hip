@@ -594,11 +594,18 @@ int submit(fv_server* S, const fv_grid_desc* desc, const double* U0, const doubl
     r->U0.assign(U0, U0 + r->hg.state_size);
     if (src) r->src.assign(src, src + r->hg.state_size);
     build_tiles(r->hg, sh, 0, 0, r->tiles, ns);
+    region_layout(r);
+    // taller tiles, with fewer partials, before the arena or the tile list is
+    // too small
+    while (sh.rows < 64 && (r->footprint > S->heap_cap || r->tiles.size() > S->tile_cap)) {
+      r->shape.rows = sh.rows = std::min(64, 2 * sh.rows);
+      build_tiles(r->hg, sh, 0, 0, r->tiles, ns);
+      region_layout(r);
+    }
   } catch (const std::bad_alloc&) {
     delete r;
     return set_error(FV_E_NOMEM, "host allocation failed");
   }
-  region_layout(r);
   if (r->footprint > S->heap_cap) {
     const size_t need = r->footprint;
     delete r;
