@@ -252,7 +252,7 @@ int fvgrid::create(HostGrid&& hg, void* d_workspace, size_t bytes, void* hip_str
   // list under the key of the kernel that runs it (a shape of the other kernel
   // fits badly: slabs as low as the Euler kernel's rows leave most of a
   // Navier-Stokes workgroup's threads without a cell)
-  for (int x = 0; x < 2; ++x) {
+  for (int x = 0; x < (g->hg.two_lists() ? 2 : 1); ++x) {
     const bool ns = g->hg.ndim == 2 && (x == 1 || !g->hg.two_lists());
     g->shape[x] = grid_shape(g->hg, ns, tune_path(nullptr), FV_FP64);
   }

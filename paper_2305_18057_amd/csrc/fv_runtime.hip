@@ -229,12 +229,24 @@ static long long ns_tiles(const HostGrid& g, int rows) {
   return t;
 }
 
+// the general 3D shape block after block, formed anew where the extents change
+// (grids of thousands of blocks mostly repeat them)
+struct GenSection {
+  int ni = 0, nj = 0, w = 0, h = 0;
+  void of(const fv_block_desc& B, int& tw, int& th) {
+    if (B.ni != ni || B.nj != nj) gen_tile_shape(ni = B.ni, nj = B.nj, w, h);
+    tw = w;
+    th = h;
+  }
+};
+
 // the most tiles build_tiles can make of a general 3D grid
 static long long max_gen_tiles(const HostGrid& g) {
   long long t = 0;
+  GenSection sec;
   for (const auto& B : g.blocks) {
     int w, h;
-    gen_tile_shape(B.ni, B.nj, w, h);
+    sec.of(B, w, h);
     t += (long long)((B.ni + w - 1) / w) * ((B.nj + h - 1) / h) * ((B.nk + kMinPlanes3D - 1) / kMinPlanes3D);
   }
   return t;
@@ -432,19 +444,6 @@ TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
     }
     return s;
   }
-  // tiles of n rows (planes), h j-rows each in 3D
-  auto tiles_of = [&](int n, int ny) {
-    long long t = 0;
-    for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
-      const fv_block_desc& B = g.blocks[b];
-      int w = 64, h = ny;
-      if (g.gen3) gen_tile_shape(B.ni, B.nj, w, h);
-      const long long ci = (B.ni + w - 1) / w;
-      t += g.ndim == 2 ? ci * ((B.nj + n - 1) / n)
-                       : ci * ((B.nj + h - 1) / h) * ((B.nk + n - 1) / n);
-    }
-    return t;
-  };
   if (g.ndim == 2 && ns) {
     // one slab, and twice as many while eight tiles per CU are left: the three
     // workgroups of a CU drift apart and fill each other's waits, so even
@@ -465,6 +464,15 @@ TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
   int nmax = 1;
   for (int b = 0; b < g.nblocks - g.nphantom; ++b)
     nmax = std::max(nmax, g.ndim == 2 ? g.blocks[b].nj : g.blocks[b].nk);
+  // tiles of each block's cross-section (formed once: a grid may have thousands
+  // of blocks), and of the grid with n rows (planes)
+  std::vector<long long> cross(g.nblocks - g.nphantom);
+  auto tiles_of = [&](int n) {
+    long long t = 0;
+    for (size_t b = 0; b < cross.size(); ++b)
+      t += cross[b] * (((g.ndim == 2 ? g.blocks[b].nj : g.blocks[b].nk) + n - 1) / n);
+    return t;
+  };
   const RoundModel* M = g.ndim == 2 ? &kRounds2D : (g.gen3 ? &kRounds3DG : &kRounds3D7);
   double best = -1.0;
   for (int ny : {7, 3}) {
@@ -472,9 +480,16 @@ TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
       if (g.ndim == 2 || g.gen3) break;
       M = &kRounds3D3;
     }
+    GenSection sec;
+    for (size_t b = 0; b < cross.size(); ++b) {
+      const fv_block_desc& B = g.blocks[b];
+      int w = 64, h = g.ndim == 2 ? B.nj : ny;
+      if (g.gen3) sec.of(B, w, h);
+      cross[b] = (long long)((B.ni + w - 1) / w) * ((B.nj + h - 1) / h);
+    }
     for (int parts = (nmax + 63) / 64; parts <= nmax; ++parts) {
       const int n = (nmax + parts - 1) / parts;
-      const double t = model_us(*M, tiles_of(n, ny), n);
+      const double t = model_us(*M, tiles_of(n), n);
       if (best < 0.0 || t < best) {
         best = t;
         s.rows = n;
@@ -492,6 +507,7 @@ void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int bof
                  std::vector<fvk::DevTile>& out, bool ns) {
   out.clear();
   int local = 0;
+  GenSection sec;
   for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
     const fv_block_desc& B = g.blocks[b];
     if (g.ndim == 2) {
@@ -519,7 +535,7 @@ void build_tiles(const HostGrid& g, const TileShape& sh, int inst_index, int bof
       // at most 64 planes: the kernel keeps a row's right-edge fluxes in 64 LDS slots, one per plane
       const int P = std::min(64, std::max(kMinPlanes3D, sh.rows));
       int NX = 64, NY = sh.ny >= 7 ? 7 : 3;
-      if (g.gen3) gen_tile_shape(B.ni, B.nj, NX, NY);
+      if (g.gen3) sec.of(B, NX, NY);
       for (int k0 = 0; k0 < B.nk; k0 += P)
         for (int j0 = 0; j0 < B.nj; j0 += NY)
           for (int i0 = 0; i0 < B.ni; i0 += NX) {
