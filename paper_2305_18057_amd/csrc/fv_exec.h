@@ -1,7 +1,7 @@
 // Launch sequencing shared by the grid API and the server: a step plan is a
-// set of tile lists (2D, 3D with 4 or 8 rows per tile) over one block table
-// and one instance table.  One step = stage 1, 2, 3 over every list, then the
-// per-instance finalize.  Steps are replayed from captured hipGraphs.
+// set of tile lists (2D, uniform 3D with 3 or 7 rows per tile, general 3D) over
+// one block table and one instance table.  One step = the stages of the scheme
+// over every list, then the per-instance finalize.  Steps are replayed from captured hipGraphs.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -13,7 +13,8 @@
 namespace fvexec {
 
 // tile sets: 2D, 3D with 3 j-rows per tile (4-wave workgroups), 3D with 7
-// (8 waves), general 3D (curvilinear blocks or a source; 4 j-rows, 4 waves)
+// (8 waves), general 3D (curvilinear blocks, oriented links or a source; tiles
+// shaped to the block, 4 waves)
 // kSet2DNS: 2D tiles that always take the Navier-Stokes stage kernel (the
 // server's viscous instances; a grid's own plan chooses by StepPlan::ns)
 enum { kSet2D = 0, kSet3D3 = 1, kSet3D7 = 2, kSet3DG = 3, kSet2DNS = 4 };

@@ -24,9 +24,9 @@
 // Two barriers per slab.  What the update needs of the slab's LDS (volume,
 // own state) is read before the second one, so a wave may stage the next slab
 // while others still update.
-// Bound by VALU issue (about 970 instructions per cell-stage, half of the issue
+// Bound by VALU issue (1126 instructions per cell-stage, 46% of the issue
 // slots) and by the latency of a slab's loads.  A stage of the 524,288-cell grid
-// takes 29 us; 53 us with 64 x 4 slabs staged in six dependent load rounds, 37
+// takes 30 us; 53 us with 64 x 4 slabs staged in six dependent load rounds, 37
 // us with all loads of those slabs at once.  Tiles on a block's faces, whose
 // ghosts take a chain of lookups, go first in each XCD's part of the list and
 // read their face rules with scalar loads: 97 us a step against 130 with 16 x

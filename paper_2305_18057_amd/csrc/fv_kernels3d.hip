@@ -17,9 +17,9 @@
 //     residual for the next plane.
 // One workgroup barrier per plane (plane and j-face fluxes are double-buffered
 // in LDS); every face flux of the tile is formed once (tile edges aside).
-// Bound by VALU issue and the waits two waves per SIMD leave open (674
-// instructions per cell-stage, 53% of the issue slots; 861 before the flux and
-// the limiter were regrouped): a middle stage of 256^3 cells 676 -> 612 us.
+// Bound by VALU issue and the waits two waves per SIMD leave open (710
+// instructions per cell-stage, 56% of the issue slots; 861 before the flux and
+// the limiter were regrouped): a stage of 256^3 cells 612 -> 556 us on average.
 // Loads for the next plane are issued one plane ahead at addresses inside the
 // arrays; ghost cells are resolved to their source before the load and
 // corrected after it.
@@ -523,9 +523,9 @@ __device__ void tile3d(const DevTile& tl, const DevBlock* __restrict__ blocks, D
   step(Tr(), F(), Tr(), 0, qb0, qb1, qb2, qb3, eb0, eb1);
   // four planes per pass with the roles renamed, so that the window needs no
   // register moves; after four planes the roles are back where they started.
-  // The stage kinds with the time-step limit keep the moves: their renamed
-  // pass takes 231 registers instead of 207 and is no faster (three steps of
-  // 256^3 cells 5.89 and 5.87 ms, runs differing by 0.5%).
+  // The stage kinds with the time-step limit keep the moves: with the limit's
+  // registers the renamed pass of the last SSP-RK3 stage spills in FP64 (55
+  // registers, 160 bytes a lane, against 209 registers and none).
   int r = 1;
   for (; !SK::cfl && r + 4 <= n; r += 4) {
     step(F(), F(), F(), r, qb0, qb1, qb2, qb3, eb0, eb1);

@@ -22,9 +22,10 @@
 //     1/3 of the sum of (outward area vector . face centre);
 //   - the halo of plane k+1, nodes of plane k+2 and the column's state at
 //     k+3 are loaded while plane k is computed.
-// Bound by VALU issue (1.25 k instructions per cell-stage, 55% of the issue
+// Bound by VALU issue (1.25 k instructions per cell-stage, 52% of the issue
 // slots; 1.62 k and 49% with 64 x 4 tiles, whose lanes beyond a block of 96
-// columns idled): two steps of 2 x 96 x 192 x 192 cells with a source, state
+// columns idled).  The stage kinds with the time-step limit fill all 256
+// registers and spill 12 to 16 bytes a lane.  Against those tiles, two steps of 2 x 96 x 192 x 192 cells with a source, state
 // copied in and out, 4.51 -> 3.28 ms; five of three 41 x 50 x 45 blocks 2.12
 // -> 1.58 ms.
 // Every face flux of a tile is formed once (tile edges aside); a face shared

@@ -35,7 +35,8 @@ hipError_t launch_cfl3d(int grid, int block, hipStream_t s, const DevTile* tiles
 const void* stage3d_kernel_ptr(int mode, int fp32, int ny);
 
 // general 3D stage (curvilinear blocks, source term; one 256-thread
-// workgroup per tile of 4 j-rows); the same stage kinds and arguments
+// workgroup per tile of columns x rows shaped to its block); the same stage
+// kinds and arguments
 hipError_t launch_stage3d_gen(int mode, int fp32, int grid, hipStream_t s, const DevTile* tiles,
                               const int* ntiles, int ntiles_fixed, int lim_fixed,
                               const DevBlock* blocks, DevInstance* insts, double* rout);

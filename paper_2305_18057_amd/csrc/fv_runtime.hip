@@ -399,7 +399,12 @@ hipError_t upload_nodes(const HostGrid& g, char* dst, hipStream_t s) {
 // last round that fills at most half of that leaves its tiles a SIMD of their
 // own and takes c1 + b1 n.  f is paid once.  The coefficients are fitted to
 // timed sweeps of n on an MI355X (FP64; FP32-flux has the same best shapes):
-// 2D inlets of 8 k to 4.2 M cells, 3D boxes of 32^3 to 256^3.
+// 2D inlets of 8 k to 4.2 M cells, 3D boxes of 32^3 to 256^3.  Over 7 2D grids,
+// 5 boxes and 5 general 3D grids of those sizes, FP64 and FP32-flux, a step with
+// the shape it picks takes at most 3.1%, 0.1% and 1.0% longer than with the best
+// of 12 to 32 shapes.  Where it finds two shapes close they are not always: for
+// the 524,288-cell inlet it puts 8 rows 2% behind 4 (and ahead of them with b1 =
+// 1.7), the device 9% (70.8 and 65.1 us a step).
 struct RoundModel {
   int per_cu;  // tiles a CU holds at once
   double f, c, b, c1, b1;
@@ -423,8 +428,9 @@ static double model_us(const RoundModel& M, long long tiles, int n) {
 // per cell); a grid of its own gets the shape whose rounds the model finds
 // shortest.  Of the even splits of the rows (planes), at most 64 of them per
 // tile: with the fixed 4 rows or 32 x 7 planes before, a 99 x 90 x 77 box ran
-// on 78 of 256 CUs (255 us a step, now 125) and a 128 x 64 grid in
-// 32 tiles (43 us, now 33); 256^3 in five rounds where three taller ones do.
+// on 78 of 256 CUs (ten FP32-flux steps 2545 us, then 1090) and a 128 x 64 grid
+// in 32 tiles (43 us a step, then 29); 256^3 in five rounds where three taller
+// ones do.
 TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
   TileShape s;
   if (shared && !ns) {
@@ -447,9 +453,11 @@ TileShape default_shape(const HostGrid& g, bool ns, bool shared) {
   if (g.ndim == 2 && ns) {
     // one slab, and twice as many while eight tiles per CU are left: the three
     // workgroups of a CU drift apart and fill each other's waits, so even
-    // rounds matter less than a short tail (524 k cells in slabs of 4 rows: 117,
-    // 123, 123 and 134 us a step with 4, 8, 12 and 16 rows; 1.05 M: 214, 204,
-    // 211, 218)
+    // rounds matter less than a short tail (524 k cells: 112, 101, 98, 109 and
+    // 122 us a step with 4, 8, 16, 32 and 64 rows; 1.05 M: 206, 187, 185, 179
+    // and 180; 2.1 M: 391, 346, 331, 327 and 328).  Over 6 grids of 8 k to 2.1 M
+    // cells in FP64 and FP32-flux a step takes at most 4.8% longer than with the
+    // best of 17 heights
     s.rows = 1;
     s.ny = 1;
     for (int b = 0; b < g.nblocks - g.nphantom; ++b) {
