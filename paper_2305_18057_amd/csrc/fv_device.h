@@ -468,9 +468,9 @@ __host__ __device__ __forceinline__ void roe_flux_plain(const T* __restrict__ qL
 // squares of the momenta: three steps of 256^3 cells with the state copied in
 // and out 6.69 -> 6.15 ms, 20 of the 524,288-cell inlet 1470 -> 1422 us; u . m
 // costs 1.6% and nothing of that.  The kernels issue 710 and 666 instructions
-// per cell-stage (861 and 770 with the form above).  RMS error against extended precision over random face
-// states at Mach 0.1 to 4: 1.0e-16 to 1.3e-16 of the flux (4.8e-16 at Mach
-// 0.1), 1.0e-16 to 1.7e-16 (4.8e-16) with the form above.
+// per cell-stage (861 and 770 with the form above).  RMS error against extended
+// precision over random face states at Mach 0.1 to 4: 1.0e-16 to 1.3e-16 of the
+// flux (4.8e-16 at Mach 0.1), 1.0e-16 to 1.7e-16 (4.8e-16) with the form above.
 // A density below zero gives NaN, as the roots of the form above do.
 template <int ND, int AX>
 __host__ __device__ __forceinline__ void roe_flux_f64(const double* __restrict__ qL,

@@ -1,7 +1,8 @@
 // Launch sequencing shared by the grid API and the server: a step plan is a
 // set of tile lists (2D, uniform 3D with 3 or 7 rows per tile, general 3D) over
 // one block table and one instance table.  One step = the stages of the scheme
-// over every list, then the per-instance finalize.  Steps are replayed from captured hipGraphs.
+// over every list, then the per-instance finalize.  Steps are replayed from
+// captured hipGraphs.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -26,9 +26,10 @@ fvk::DevInstance* take_record() {
   std::lock_guard<std::mutex> lk(g_rec_mu);
   if (!g_rec_free) {
     char* slab = nullptr;
-    // portable: handles of every device draw on it
-    if (hipHostMalloc((void**)&slab, kRecordStride * kSlabRecords, hipHostMallocPortable) != hipSuccess)
-      return nullptr;
+    // portable: handles of every device draw on it; coherent, as memory that is
+    // asked for without flags is: the host reads a record once its stream is done
+    const unsigned flags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+    if (hipHostMalloc((void**)&slab, kRecordStride * kSlabRecords, flags) != hipSuccess) return nullptr;
     for (int k = 0; k < kSlabRecords; ++k) {
       void* r = slab + k * kRecordStride;
       *(void**)r = g_rec_free;
